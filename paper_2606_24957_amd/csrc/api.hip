@@ -301,6 +301,17 @@ size_t score_ws_bytes(size_t rows, size_t cols, size_t chunk) {
          round_up(rows * n_chunks * 2 * sizeof(float), kAlign);
 }
 
+// Bytes of K rows one buffer resource covers (a sequence's rows, or the page pool) up to the
+// last used KV head's; -1 when a row lies past 2^31 bytes.
+int64_t score_extent(const ScoreArgs& a, int last_kv, int row_dim) {
+  const int64_t rows_bytes = a.k.page_table
+                                 ? (int64_t)(a.k.num_pages - 1) * a.k.stride_page * 2 +
+                                       (int64_t)((1 << a.k.page_shift) - 1) * a.k.stride_n * 2
+                                 : (a.k.capacity - 1) * a.k.stride_n * 2;
+  const int64_t extent = rows_bytes + (int64_t)last_kv * a.k.stride_h * 2 + (int64_t)row_dim * 2;
+  return rows_bytes < 0 || extent > INT32_MAX ? -1 : extent;
+}
+
 // The single-pass form (score_sync.hip) for a call with at most 16 (head, query) pairs over
 // at most 4 KV heads, one output group and one output (a's heads, layers, cache view, dims,
 // output and workspace fields set): fills sc and returns true, or false when the call
@@ -347,14 +358,8 @@ bool score_sync_plan(const ScoreArgs& a, int32_t n_heads, int32_t nq_max, int ro
   }
   if (chunks > kScoreSyncMaxChunks || (int64_t)B * chunks > kScoreSyncCUs) return false;
   if ((size_t)a.n_layers * B * chunks * 16 * 2 * sizeof(float) > logits_bytes) return false;
-  // every K row the kernel reads lies within 2^31 bytes of its buffer resource's base (a
-  // sequence's rows, or the page pool)
-  const int64_t rows_bytes = a.k.page_table
-                                 ? (int64_t)(a.k.num_pages - 1) * a.k.stride_page * 2 +
-                                       (int64_t)((1 << a.k.page_shift) - 1) * a.k.stride_n * 2
-                                 : (a.k.capacity - 1) * a.k.stride_n * 2;
-  const int64_t extent = rows_bytes + (int64_t)sc.kv[nu - 1] * a.k.stride_h * 2 + (int64_t)row_dim * 2;
-  if (rows_bytes < 0 || extent > INT32_MAX) return false;
+  const int64_t extent = score_extent(a, sc.kv[nu - 1], row_dim);
+  if (extent < 0) return false;
   for (int l = 0; l < a.n_layers; ++l) {
     sc.q_layers[l] = a.q_layers[l];
     sc.k_layers[l] = a.k_layers[l];
@@ -381,6 +386,80 @@ bool score_sync_plan(const ScoreArgs& a, int32_t n_heads, int32_t nq_max, int ro
   // a sequence's chunks on one XCD when they fit there with the other sequences of that XCD
   sc.local = (B + 7) / 8 * chunks <= kScoreSyncCUs / 8 ? 1 : 0;
   sc.extent = (int32_t)extent;
+  return true;
+}
+
+// The call by chunks of four-wave workgroups (score_once.hip, score_reread.hip), for one output
+// group, positions as rows and pairs that fit the column tiles of their KV heads (a's heads,
+// layers, cache view, dims and output fields set): fills cc, the workspace, chunk and stats
+// fields aside, and returns true, or false when neither form takes the call.
+bool score_chunk_call(const ScoreArgs& a, int32_t n_heads, int32_t nq_max, int row_dim, int B, int32_t groups,
+                      ChunkCall& cc) {
+  if (a.page_mode || groups != 1 || (row_dim != 64 && row_dim != 128)) return false;
+  memset(&cc, 0, sizeof cc);
+  // used KV heads in ascending order, and the pairs of each
+  int nu = 0, pairs[4] = {0, 0, 0, 0};
+  for (int i = 0; i < n_heads; ++i) {
+    const int g = a.heads[i] / a.group_size;
+    int at = 0;
+    while (at < nu && cc.kv[at] < g) ++at;
+    if (at == nu || cc.kv[at] != g) {
+      if (nu == 4) return false;
+      for (int v = nu; v > at; --v) {
+        cc.kv[v] = cc.kv[v - 1];
+        pairs[v] = pairs[v - 1];
+      }
+      cc.kv[at] = g;
+      pairs[at] = 0;
+      ++nu;
+    }
+    pairs[at] += nq_max;
+  }
+  // one column tile for all KV heads where every pair fits it, else nt for each KV head
+  int nt = 0;
+  if (n_heads * nq_max > 16)
+    for (int u = 0; u < nu; ++u) nt = (pairs[u] + 15) / 16 > nt ? (pairs[u] + 15) / 16 : nt;
+  if (nt * nu > kChunkMaxTiles) return false;
+  for (int u = 0; u < nu; ++u) {
+    int at = 0;  // the pair's place among those of its KV head
+    for (int i = 0; i < n_heads; ++i) {
+      if (a.heads[i] / a.group_size != cc.kv[u]) continue;
+      for (int jq = 0; jq < nq_max; ++jq, ++at) {
+        const int t = nt == 0 ? 0 : u * nt + at / 16;
+        const int col = t * 16 + cc.cols[t]++;
+        cc.col_head[col] = a.heads[i];
+        cc.col_query[col] = (uint8_t)jq;
+        cc.col_u[col] = (uint8_t)u;
+      }
+    }
+  }
+  for (int t = 0; t < kChunkMaxTiles; ++t)
+    if (cc.cols[t] == 0) cc.col_head[t * 16] = a.heads[0];  // an empty tile repeats a pair at weight zero
+  const int64_t extent = score_extent(a, cc.kv[nu - 1], row_dim);
+  if (extent < 0) return false;
+  for (int l = 0; l < a.n_layers; ++l) {
+    cc.q_layers[l] = a.q_layers[l];
+    cc.k_layers[l] = a.k_layers[l];
+  }
+  cc.q_sb = a.q_sb;
+  cc.q_sj = a.q_sj;
+  cc.q_sh = a.q_sh;
+  cc.k = a.k;
+  cc.dims = a.dims;
+  cc.init = a.init;
+  cc.init_sb = a.init_sb;
+  cc.out = a.out;
+  cc.out_sb = a.out_sb;
+  cc.out_sl = a.out_sl;
+  cc.stats = a.logits;  // statistics go where the two-pass form's logits do
+  cc.scale_log2 = a.scale_log2;
+  cc.batch = B;
+  cc.n_layers = a.n_layers;
+  cc.per_layer = a.per_layer;
+  cc.head_dim = row_dim;
+  cc.nu = nu;
+  cc.nt = nt;
+  cc.extent = (int32_t)extent;
   return true;
 }
 
@@ -447,9 +526,88 @@ struct ScorePrep {
   ScoreArgs a;
   int n_groups = 0, max_group = 0, row_dim = 0, B = 0;
   bool empty = false;  // nothing to compute
-  bool sync = false;
-  SyncCall sc;
+  enum Form { kTwoPass, kSync, kOnce, kReread } form = kTwoPass;
+  SyncCall sc;   // kSync
+  ChunkCall cc;  // kOnce, kReread
 };
+
+// The form of a call whose two-pass arguments P.a are filled, for `cols` positions at most.
+// MI355X, 4 + 3 layers' calls of a step at the Qwen2.5-72B shape unless said otherwise:
+//   single pass, 16-wave workgroups (score_sync.hip): at most 16 pairs, from 393216 positions of
+//     all sequences on while the chunks of 2048 fit the chip in one round.
+//   single pass, small calls (score_once.hip): a target call up to one 512-position chunk per CU
+//     (131072 positions: 38 us against 44 in two passes; past them a second workgroup on some
+//     CUs makes it 51 against 43); a draft's three layers up to two (262144: 61 us against 69),
+//     and with 17 to 32 pairs, whose logits make two passes longer, up to four (8 x 65536, 24
+//     pairs: 127 us against 155; past them a ragged batch has several rounds of workgroups
+//     of sequences that end apart, 177 us against 164 at 16 x up to 62922).  Chunks of 256 positions fill the chip better
+//     up to 32768 positions (both calls 21 us against 24), those of 512 beyond.  Per-layer
+//     outputs and single layers of more than 16 pairs, whose count of layers must not decide
+//     (a layer has the same bits in a call of its own): up to 8192 positions.
+//   K read twice (score_reread.hip): 33 to 64 pairs from 131072 positions on (24 layers of
+//     16 x 32768: 1180 us against 2020).
+//   two passes (score.hip): everything else.
+void score_choose(ScorePrep& P, int row_dim, int B, int32_t nq_max, int64_t cols, int32_t groups, int32_t* sync_region,
+                  size_t logits_bytes) {
+  const ScoreArgs& a = P.a;
+  const bool sync = score_sync_plan(a, a.n_heads, nq_max, row_dim, B, cols, groups, sync_region, logits_bytes, P.sc);
+  if (sync && P.sc.tw == 8) {
+    P.form = ScorePrep::kSync;
+    return;
+  }
+  ChunkCall& cc = P.cc;
+  if (score_chunk_call(a, a.n_heads, nq_max, row_dim, B, groups, cc)) {
+    cc.sync = sync_region;
+    const int64_t units = (int64_t)B * (a.per_layer ? a.n_layers : 1), chunks8 = (cols + 511) / 512;
+    const int tiles = cc.nt == 0 ? 1 : cc.nu * cc.nt;
+    int64_t most;  // chunks of 512 positions, all sequences
+    if (a.per_layer || (a.n_layers == 1 && cc.nt > 0)) most = 16;
+    else if (a.n_layers == 1) most = kScoreSyncCUs;
+    else most = cc.nt == 0 ? 2 * kScoreSyncCUs : 4 * kScoreSyncCUs;
+    cc.tw = B * chunks8 <= 64 || most == 16 ? 4 : 8;
+    const int64_t chunks = (cols + 64 * cc.tw - 1) / (64 * cc.tw);
+    const int once_cols = 16 * tiles * (a.per_layer ? 1 : a.n_layers);
+    if (score_once_supported(cc) && B * chunks8 <= most && chunks <= kChunkMaxOnce && units <= kScoreSyncMaxBatch &&
+        units * chunks <= INT32_MAX / 2 && (size_t)units * (chunks + 1) * once_cols * 2 * sizeof(float) <= logits_bytes) {
+      cc.chunks = (int32_t)chunks;
+      cc.share_merge = B * chunks <= 2 * kScoreSyncCUs ? 1 : 0;
+      P.form = ScorePrep::kOnce;
+      return;
+    }
+    // chunks of 1024 positions, or of 512 where those would leave a CU less than two
+    cc.tw = B * chunks8 <= 2 * kScoreSyncCUs ? 8 : 16;
+    const int64_t rchunks = (cols + 64 * cc.tw - 1) / (64 * cc.tw);
+    if (score_reread_supported(cc) && B * chunks8 >= kScoreSyncCUs && (int64_t)B * a.n_layers <= kScoreSyncMaxBatch &&
+        (size_t)B * a.n_layers * (rchunks + 1) * 16 * tiles * 2 * sizeof(float) <= logits_bytes &&
+        2 * units * rchunks * (a.n_layers + 1) <= INT32_MAX) {
+      cc.chunks = (int32_t)rchunks;
+      P.form = ScorePrep::kReread;
+      return;
+    }
+  }
+  if (sync) P.form = ScorePrep::kSync;
+}
+
+// The launch arguments of one or two calls of score_once.hip, or of one of score_reread.hip.
+ChunkArgs score_chunk_args(const ChunkCall* c0, const ChunkCall* c1) {
+  ChunkArgs ca;
+  memset(&ca, 0, sizeof ca);
+  int n = 0;
+  for (const ChunkCall* c : {c0, c1}) {
+    if (!c) continue;
+    ca.call[n++] = *c;
+    const int units = c->batch * (c->per_layer ? c->n_layers : 1);
+    ca.units = units > ca.units ? units : ca.units;
+  }
+  // the second kind's blocks come `lag` units behind the first's: about as many blocks as the
+  // chip holds, so that they find their columns merged (16 x 32768 positions, 4 layers: 252 us;
+  // a quarter of that lag 344)
+  const int64_t blocks = (int64_t)(c0->per_layer ? 1 : c0->n_layers) * c0->chunks;
+  int64_t lag = (4 * kScoreSyncCUs + blocks - 1) / blocks;
+  if (lag > ca.units) lag = ca.units;
+  ca.lag = (int32_t)lag;
+  return ca;
+}
 
 // Fills the output, size and workspace fields of P.a (heads, layers, k view, dims already
 // set) for `cols` rows per sequence at most, and plans the single-pass form.
@@ -478,21 +636,29 @@ dustin_status score_fill(ScorePrep& P, int row_dim, int B, int32_t nq_max, int64
   a.stats = reinterpret_cast<float*>(base + kScoreSyncBytes + logits_bytes);
   P.row_dim = row_dim;
   P.B = B;
-  P.sync = score_sync_plan(a, a.n_heads, nq_max, row_dim, B, cols, groups, reinterpret_cast<int32_t*>(base),
-                           logits_bytes, P.sc);
+  score_choose(P, row_dim, B, nq_max, cols, groups, reinterpret_cast<int32_t*>(base), logits_bytes);
   return DUSTIN_OK;
 }
 
 dustin_status score_run(const ScorePrep& P, void* stream) {
   if (P.empty) return DUSTIN_OK;
   hipError_t e;
-  if (P.sync) {
-    SyncArgs sa;
-    memset(&sa, 0, sizeof sa);
-    sa.call[0] = P.sc;
-    e = launch_score_sync(sa, static_cast<hipStream_t>(stream));
-  } else {
-    e = launch_score(P.a, P.B, P.n_groups, P.max_group, P.row_dim, static_cast<hipStream_t>(stream));
+  switch (P.form) {
+    case ScorePrep::kSync: {
+      SyncArgs sa;
+      memset(&sa, 0, sizeof sa);
+      sa.call[0] = P.sc;
+      e = launch_score_sync(sa, static_cast<hipStream_t>(stream));
+      break;
+    }
+    case ScorePrep::kOnce:
+      e = launch_score_once(score_chunk_args(&P.cc, nullptr), 1, static_cast<hipStream_t>(stream));
+      break;
+    case ScorePrep::kReread:
+      e = launch_score_reread(score_chunk_args(&P.cc, nullptr), static_cast<hipStream_t>(stream));
+      break;
+    default:
+      e = launch_score(P.a, P.B, P.n_groups, P.max_group, P.row_dim, static_cast<hipStream_t>(stream));
   }
   return e == hipSuccess ? DUSTIN_OK : DUSTIN_ERR_LAUNCH;
 }
@@ -632,17 +798,23 @@ dustin_status dustin_score_calls(int32_t n_calls, const dustin_score_call* calls
     if (c.digit_hist && !aligned(c.digit_hist, 16)) return DUSTIN_ERR_INVALID_ARG;
     P[i].a.hist = c.digit_hist;
     P[i].sc.hist = c.digit_hist;
+    P[i].cc.hist = c.digit_hist;
   }
   if (n_calls == 2 && calls[0].digit_hist && calls[0].digit_hist == calls[1].digit_hist) return DUSTIN_ERR_INVALID_ARG;
   if (n_calls == 2 && calls[0].workspace == calls[1].workspace) return DUSTIN_ERR_WORKSPACE;
-  if (n_calls == 2 && P[0].sync && P[1].sync && !P[0].empty && !P[1].empty &&
-      score_sync_pair_supported(P[0].sc, P[1].sc)) {
+  const bool both = n_calls == 2 && !P[0].empty && !P[1].empty && P[0].form == P[1].form;
+  if (both && P[0].form == ScorePrep::kSync && score_sync_pair_supported(P[0].sc, P[1].sc)) {
     SyncArgs sa;
     memset(&sa, 0, sizeof sa);
     sa.call[0] = P[0].sc;
     sa.call[1] = P[1].sc;
     return launch_score_sync_pair(sa, static_cast<hipStream_t>(stream)) == hipSuccess ? DUSTIN_OK
                                                                                       : DUSTIN_ERR_LAUNCH;
+  }
+  if (both && P[0].form == ScorePrep::kOnce && score_once_pair_supported(P[0].cc, P[1].cc)) {
+    const hipError_t e =
+        launch_score_once(score_chunk_args(&P[0].cc, &P[1].cc), 2, static_cast<hipStream_t>(stream));
+    return e == hipSuccess ? DUSTIN_OK : DUSTIN_ERR_LAUNCH;
   }
   for (int i = 0; i < n_calls; ++i) {
     const dustin_status st = score_run(P[i], stream);

@@ -143,6 +143,55 @@ hipError_t launch_score_sync(const SyncArgs& a, hipStream_t stream);
 bool score_sync_pair_supported(const SyncCall& c0, const SyncCall& c1);
 hipError_t launch_score_sync_pair(const SyncArgs& a, hipStream_t stream);
 
+// ---- score calls by chunks of four-wave workgroups (score_once.hip, score_reread.hip) ----
+constexpr int kChunkWaves = 4;
+constexpr int kChunkMaxTW = 16;            // most 16-position tiles per wave
+constexpr int kChunkMaxOnce = 256;         // most chunks of a sequence in score_once.hip
+constexpr int kChunkMaxTiles = 4;          // most column tiles of 16 pairs
+constexpr int kChunkMaxQ = 12;             // most column tiles times layers that one output sums (score_reread.hip)
+
+// One call: column i < cols[t] of column tile t is the pair (query head col_head, query
+// col_query)[16 t + i] on used KV head kv[col_u]; nt = 0: one tile for the pairs of all nu KV
+// heads, else tiles u nt .. u nt + nt - 1 belong to KV head kv[u].  A sequence has at most
+// `chunks` chunks of 64 tw positions.
+struct ChunkCall {
+  const uint16_t* q_layers[kScoreMaxLayers];
+  const uint16_t* k_layers[kScoreMaxLayers];
+  int64_t q_sb, q_sj, q_sh;
+  KvView k;
+  SeqDims dims;
+  const float* init;
+  int64_t init_sb;
+  float* out;
+  int64_t out_sb, out_sl;
+  float* stats;   // (max, sum of exp2) of every chunk and column
+  int32_t* sync;  // the workspace's counter region (zero between calls) and timeout flag
+  float scale_log2;
+  int32_t batch, n_layers, per_layer, head_dim, nu, nt, tw, chunks;
+  int32_t share_merge;  // score_once.hip: every workgroup of the call gets a slot at once
+  int32_t extent;  // bytes of K rows one buffer resource covers (a sequence, or the page pool)
+  int32_t kv[4];
+  int32_t cols[kChunkMaxTiles];
+  int32_t col_head[16 * kChunkMaxTiles];
+  uint8_t col_query[16 * kChunkMaxTiles], col_u[16 * kChunkMaxTiles];
+  uint32_t* hist;  // optional: as ScoreArgs::hist (one output row per sequence)
+};
+
+struct ChunkArgs {
+  ChunkCall call[2];
+  int32_t units, lag;  // the launcher's: score_once.hip, score_reread.hip
+};
+static_assert(sizeof(ChunkArgs) <= 4096, "kernel arguments stay within 4 KiB");
+
+// small calls in one pass (score_once.hip): one call, or two in one launch
+bool score_once_supported(const ChunkCall& c);
+bool score_once_pair_supported(const ChunkCall& c0, const ChunkCall& c1);
+hipError_t launch_score_once(const ChunkArgs& a, int n_calls, hipStream_t stream);
+
+// calls that read K twice (score_reread.hip)
+bool score_reread_supported(const ChunkCall& c);
+hipError_t launch_score_reread(const ChunkArgs& a, hipStream_t stream);
+
 // ---- attention recovery rate (arr.hip) ----
 struct ArrArgs {
   const float* s;  // Eq. 5 score over the served heads and the window's queries

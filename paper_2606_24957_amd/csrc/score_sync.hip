@@ -1,5 +1,6 @@
 // score_sync.hip -- Eq. 5 in one pass, for calls whose (head, query) pairs fit one MFMA
-// column tile.
+// column tile and whose chunks fill the chip in one round (score_once.hip takes the smaller ones
+// of the common shapes).
 //
 // The two-pass form (score.hip) writes every pair's logits to the workspace and reads them
 // back, because the softmax of Eq. 5 needs each pair's max and sum over all N_b positions
@@ -429,16 +430,13 @@ hipError_t launch_score_sync(const SyncArgs& a, hipStream_t stream) {
 // one verification step scores them); false when the two calls have another pair.
 bool score_sync_pair_supported(const SyncCall& c0, const SyncCall& c1) {
   return c0.head_dim == 128 && c0.nu == 4 && c1.head_dim == 64 && c1.nu == 2 && c0.tw == c1.tw &&
-         (c0.tw == 8 || c0.tw == 2) && (c0.k.page_table != nullptr) == (c1.k.page_table != nullptr);
+         c0.tw == 8 && (c0.k.page_table != nullptr) == (c1.k.page_table != nullptr);
 }
 
 hipError_t launch_score_sync_pair(const SyncArgs& a, hipStream_t stream) {
   const bool paged = a.call[0].k.page_table != nullptr;
-  if (a.call[0].tw == 8)
-    return paged ? launch_sync<SyncShape<128, 4, 8, true>, SyncShape<64, 2, 8, true>>(a, stream)
-                 : launch_sync<SyncShape<128, 4, 8, false>, SyncShape<64, 2, 8, false>>(a, stream);
-  return paged ? launch_sync<SyncShape<128, 4, 2, true>, SyncShape<64, 2, 2, true>>(a, stream)
-               : launch_sync<SyncShape<128, 4, 2, false>, SyncShape<64, 2, 2, false>>(a, stream);
+  return paged ? launch_sync<SyncShape<128, 4, 8, true>, SyncShape<64, 2, 8, true>>(a, stream)
+               : launch_sync<SyncShape<128, 4, 8, false>, SyncShape<64, 2, 8, false>>(a, stream);
 }
 
 }  // namespace dustin

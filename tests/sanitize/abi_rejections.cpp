@@ -18,6 +18,11 @@ hipError_t launch_score(const ScoreArgs&, int, int, int, int, hipStream_t) { ret
 hipError_t launch_score_sync(const SyncArgs&, hipStream_t) { return hipErrorInvalidValue; }
 bool score_sync_pair_supported(const SyncCall&, const SyncCall&) { return false; }
 hipError_t launch_score_sync_pair(const SyncArgs&, hipStream_t) { return hipErrorInvalidValue; }
+bool score_once_supported(const ChunkCall&) { return true; }
+bool score_once_pair_supported(const ChunkCall&, const ChunkCall&) { return true; }
+hipError_t launch_score_once(const ChunkArgs&, int, hipStream_t) { return hipErrorInvalidValue; }
+bool score_reread_supported(const ChunkCall&) { return true; }
+hipError_t launch_score_reread(const ChunkArgs&, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_arr(const ArrArgs&, int, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_page_meta(const PageMetaArgs&, int, int, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_topk(const TopkArgs&, int, hipStream_t) { return hipErrorInvalidValue; }

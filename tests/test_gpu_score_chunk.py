@@ -1,0 +1,153 @@
+"""The score's chunk forms against the oracle at the edges of their rules: small calls in one
+pass (score_once.hip) with chunks of 256 and of 512 positions, one layer and a draft's three, one
+shared column tile and one per KV head; and K read twice (score_reread.hip) with chunks of 512
+and of 1024 positions, summed, per layer and counted by top key digit.  Lengths sit on, before
+and after chunk and tile edges, with empty sequences, per-sequence query counts (none among
+them), permuted pages, and scales of either sign and zero."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import paper_2606_24957_amd as D
+from tests.gpu_util import bits, check_score, host, scale_of
+from tests.test_gpu_score_single_pass import _paged, _sync_region_clear
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+TARGET = (64, 8, 128, [0, 17, 34, 51])
+DRAFT = (14, 2, 64, [0, 4, 7, 11])
+ALL = (14, 2, 64, list(range(14)))
+
+
+def _inputs(model, lens, nq, n_layers, seed, page_size=0):
+    Hq, Hkv, d, _ = model
+    B, N = len(lens), max(lens)
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    qs = [torch.randn((B, max(nq), Hq, d), generator=g, device=DEV).to(torch.bfloat16) for _ in range(n_layers)]
+    ks = [torch.randn((B, N, Hkv, d), generator=g, device=DEV).to(torch.bfloat16) for _ in range(n_layers)]
+    kin, pt = ks, None
+    if page_size:
+        pairs = [_paged(k, page_size, seed + 1) for k in ks]
+        kin, pt = [p for p, _ in pairs], pairs[0][1]
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device=DEV)
+    return qs, ks, kin, pt, i32(lens), i32(nq)
+
+
+def _reference(model, q, k, lens, nq, scale, check):
+    """Per checked sequence the fp64-computed score of one layer."""
+    Hq, Hkv, d, heads = model
+    return {b: O.score(bits(q[b:b + 1]), bits(k[b:b + 1, :max(lens[b], 1)]), [lens[b]], [nq[b]], heads, scale,
+                       num_kv_heads=Hkv)[0, 0, :lens[b]].astype(np.float64) for b in check}
+
+
+def _check(out, refs, lens, label):
+    got = host(out)
+    for b, n in enumerate(lens):
+        assert np.all(got[b, 0, n:] == -5.0), f"{label}: positions past N_b of sequence {b} written"
+        if b in refs:
+            check_score(got[b, 0, :n], refs[b], n, f"{label} b={b} N_b={n}")
+
+
+SMALL = [0, 1, 16, 255, 256, 257, 1023]                  # chunks of 256
+LARGE = [11300, 512, 513, 511, 7, 0, 1025, 10000, 4097]  # 9 x 23 chunks of 512
+
+
+@pytest.mark.parametrize("model,n_layers,nq_max,lens,page_size", [
+    (TARGET, 1, 1, SMALL, 0), (TARGET, 1, 1, LARGE, 0), (TARGET, 1, 4, LARGE, 16),
+    (DRAFT, 3, 4, SMALL, 0), (DRAFT, 3, 4, LARGE, 0), (DRAFT, 3, 3, SMALL, 4),
+    (DRAFT, 3, 5, SMALL, 0), (DRAFT, 3, 6, LARGE, 16), (DRAFT, 3, 8, LARGE, 0),
+    (DRAFT, 1, 8, SMALL, 0), (ALL, 1, 4, SMALL, 0), (ALL, 1, 3, SMALL, 64),
+])
+def test_small_calls_in_one_pass(model, n_layers, nq_max, lens, page_size):
+    nq = [max(0, nq_max - b % 3) if b else nq_max for b in range(len(lens))]
+    qs, ks, kin, pt, seq, nqt = _inputs(model, lens, nq, n_layers, 100 + len(lens) + nq_max, page_size)
+    N, d = max(lens), model[2]
+    init = torch.rand((len(lens), 1, N), generator=torch.Generator(device=DEV).manual_seed(3), device=DEV) / N
+    out = torch.full((len(lens), 1, N), -5.0, device=DEV)
+    call = D.plan_score_layers(qs, kin, seq, model[3], n_query=nqt, init=init, out=out, max_len=N, page_table=pt)
+    for _ in range(2):  # the counters return to zero
+        call()
+    torch.cuda.synchronize()
+    _sync_region_clear()
+    refs = {b: host(init)[b, 0, :n].astype(np.float64) for b, n in enumerate(lens)}
+    for q, k in zip(qs, ks):
+        for b, r in _reference(model, q, k, lens, nq, scale_of(d), range(len(lens))).items():
+            refs[b] = refs[b] + r
+    _check(out, refs, lens, "once")
+
+
+@pytest.mark.parametrize("scale", [-0.11, 0.0])
+@pytest.mark.parametrize("model,n_layers,lens", [(DRAFT, 3, [700, 33]), (ALL, 1, [66000, 2100])])
+def test_negative_and_zero_scale(scale, model, n_layers, lens):
+    nq = [4, 3]
+    qs, ks, kin, pt, seq, nqt = _inputs(model, lens, nq, n_layers, 200)
+    out = torch.full((2, 1, max(lens)), -5.0, device=DEV)
+    D.score_layers(qs, kin, seq, model[3], n_query=nqt, out=out, max_len=max(lens), scale=scale)
+    torch.cuda.synchronize()
+    _sync_region_clear()
+    refs = {b: 0.0 for b in range(2)}
+    for q, k in zip(qs, ks):
+        for b, r in _reference(model, q, k, lens, nq, scale, range(2)).items():
+            refs[b] = refs[b] + r
+    _check(out, refs, lens, f"scale {scale}")
+
+
+# 2 x 129 chunks of 512 positions: chunks of 512; 5 x 137: chunks of 1024
+REREAD = [[65700, 1, ], [70000, 1023, 0, 1025, 16]]
+
+
+@pytest.mark.parametrize("lens", REREAD)
+@pytest.mark.parametrize("n_layers,per_layer,page_size", [(1, False, 0), (2, False, 0), (3, False, 16), (3, True, 0)])
+def test_k_read_twice(lens, n_layers, per_layer, page_size):
+    nq = [4 - b % 4 for b in range(len(lens))]
+    qs, ks, kin, pt, seq, nqt = _inputs(ALL, lens, nq, n_layers, 300 + n_layers, page_size)
+    N, B = max(lens), len(lens)
+    if per_layer:
+        out = torch.full((n_layers, B, 1, N), -5.0, device=DEV)
+        for _ in range(2):
+            D.score_per_layer(qs, kin, seq, ALL[3], n_query=nqt, out=out, max_len=N, page_table=pt)
+        torch.cuda.synchronize()
+        _sync_region_clear()
+        for l in range(n_layers):
+            _check(out[l], _reference(ALL, qs[l], ks[l], lens, nq, scale_of(64), range(B) if l == 1 else range(1, B)),
+                   lens, f"layer {l}")
+            one = torch.full((B, 1, N), -5.0, device=DEV)
+            D.score(qs[l], kin[l], seq, ALL[3], n_query=nqt, out=one, max_len=N, page_table=pt)
+            assert torch.equal(one, out[l])  # a layer has the same bits in a call of its own
+        return
+    out = torch.full((B, 1, N), -5.0, device=DEV)
+    hist = D.digit_hist(B, DEV)
+    plan = D.plan_score_layers(qs, kin, seq, ALL[3], n_query=nqt, out=out, max_len=N, page_table=pt)
+    D.plan_score_calls([plan], digit_hists=[hist])()
+    torch.cuda.synchronize()
+    _sync_region_clear()
+    refs = {b: 0.0 for b in range(B)}
+    for q, k in zip(qs, ks):
+        for b, r in _reference(ALL, q, k, lens, nq, scale_of(64), range(B)).items():
+            refs[b] = refs[b] + r
+    _check(out, refs, lens, "reread")
+    got = host(out)
+    for b, n in enumerate(lens):  # positive scores: the key is the bit pattern with the sign set
+        keys = (got[b, 0, :n].view(np.uint32) | 0x80000000) >> 20
+        assert np.array_equal(np.bincount(keys, minlength=4096), host(hist)[b])
+
+
+def test_a_pair_of_small_calls_has_the_bits_of_the_separate_calls():
+    """A step's target and draft calls in one launch, 17 pairs and more, both chunk sizes."""
+    for lens in (SMALL, LARGE):
+        B, N = len(lens), max(lens)
+        qt, _, kt, _, seq, _ = _inputs(TARGET, lens, [1] * B, 1, 400)
+        nq = [6 - b % 4 for b in range(B)]
+        qd, _, kd, _, _, nqt = _inputs(DRAFT, lens, nq, 3, 401)
+        st, sd = torch.full((B, 1, N), -5.0, device=DEV), torch.full((B, 1, N), -5.0, device=DEV)
+        t = D.plan_score(qt[0], kt[0], seq, TARGET[3], out=st, max_len=N)
+        d = D.plan_score_layers(qd, kd, seq, DRAFT[3], n_query=nqt, out=sd, max_len=N, ws_tag="score_draft")
+        t()
+        d()
+        ref_t, ref_d = st.clone(), sd.clone()
+        st.fill_(-5.0)
+        sd.fill_(-5.0)
+        D.plan_score_calls([t, d])()
+        torch.cuda.synchronize()
+        assert torch.equal(st, ref_t) and torch.equal(sd, ref_d)
