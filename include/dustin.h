@@ -383,9 +383,8 @@ dustin_status dustin_topk(const float* s_draft, int64_t d_sb, int64_t d_sg,
  *        are not written.  Round to nearest even.
  *   workspace  dustin_attn_workspace(..., sparse = 1) bytes, 256-byte aligned (0 bytes,
  *        i.e. NULL, when the batch has enough (b, KV head) pairs to fill the GPU without
- *        splitting the token list).  Its first 256 KB are a counter region (one int32 per
- *        (b, KV head); B * num_kv_heads <= 65536), the partial results of token splits
- *        follow.  Zero-fill the workspace once before its first use: every call leaves the
+ *        splitting the token list).  Its first 256 KB are a counter region (B * num_kv_heads
+ *        <= 65536), the partial results of token splits follow.  Zero-fill the workspace once before its first use: every call leaves the
  *        counter region at zero again, so one buffer can then serve calls of any shape.
  *        Calls sharing a workspace must not overlap.
  * Rounding: bf16 inputs, fp32 MFMA accumulation, fp32 online softmax, probabilities

@@ -96,31 +96,49 @@ int attn_row_tiles(int nq_max, int group_size) {
   return rt < 1 ? 1 : rt;
 }
 
-// Unit slots per (b, g): enough workgroups for one per CU (256 CUs, one workgroup of four
-// waves each), each split at least 8 steps of 32 tokens (two per wave) for the longest
-// pair.  The kernel then sizes the splits from the actual per-pair lengths, so that longer
-// pairs take more of the slots; beyond kAttnBalancePairs pairs each pair is one workgroup.
-int attn_splits(int batch, int num_kv_heads, int64_t tokens_per_pair) {
+// The token splits of a launch: unit slots per (b, g) on average, and the smallest split, in steps
+// of 32 tokens, that the kernel's balancing may choose.  It sizes the splits from the actual
+// per-pair lengths, so that longer pairs take more of the slots; beyond kAttnBalancePairs
+// pairs each pair is one workgroup.
+struct AttnSplits {
+  int slots, min_steps;
+};
+
+// As many workgroups as the chip holds in one round (256 CUs, one workgroup of four waves
+// each): a few more would run in a second round (12 sequences of 8 KV heads, 2048 tokens: 2
+// splits 26.8 us, 3, 288 workgroups, 38.4; 20 sequences: one split 40.5, two 50.9), and splits
+// that share the merge wait for each other.  Each split at least eight steps (two per wave) for
+// the longest pair, or four (one per wave) where eight splits or more leave that little: one
+// sequence, 8 KV heads of 40 rows, 2048 tokens in 16 splits of four steps 14.7 us, 8 of eight 15.2,
+// 1 of 64 29.8; 1024 in 8 of four 13.5, 4 of eight 15.8.  From sixteen steps on, eight splits of
+// two: 512 tokens 13.2 us, 4 of four 14.2, one 14.2.  Below, one: 256 tokens, one KV head, 10.9, 4 of
+// two 13.9.
+AttnSplits attn_splits(int batch, int num_kv_heads, int64_t tokens_per_pair) {
   const int64_t pairs = (int64_t)batch * num_kv_heads;
-  if (pairs <= 0) return 1;
+  if (pairs <= 0 || pairs > kAttnBalancePairs) return {1, 8};
   const int64_t steps = (tokens_per_pair + 31) / 32;
-  int64_t s;
+  int64_t s, min_steps = 8;
   const int forced = env_int("DUSTIN_ATTN_SPLITS", 0);
-  if (pairs > kAttnBalancePairs) return 1;
   if (forced > 0) {
     s = forced;
+    min_steps = 1;
   } else {
-    s = (256 + pairs - 1) / pairs;
-    if (s > steps / 8) s = steps / 8;
+    s = kAttnBalancePairs / pairs;
+    if (s >= 8 && steps >= 16) min_steps = steps >= 32 ? 4 : 2;
+    int64_t most = steps / min_steps;
+    if (min_steps == 2) most = 8;
+    if (s > most) s = most;
   }
   if (s > kAttnMaxSplits) s = kAttnMaxSplits;
   if (s > steps) s = steps;
-  return s < 1 ? 1 : (int)s;
+  return {s < 1 ? 1 : (int)s, (int)min_steps};
 }
 
-// Split workspace: a fixed counter region first (one int32 per (b, g) for up to
-// kAttnMaxPairs pairs, zero between calls whatever shape used it last), then the partials.
+// Split workspace: a fixed counter region first (the arrival counters and marks of up to
+// kAttnBalancePairs split pairs, zero between calls whatever shape used it last), then the
+// partials.
 constexpr int64_t kAttnMaxPairs = 65536;
+static_assert(2 * kAttnMaskOffset <= kAttnMaxPairs, "the counters and marks of split pairs");
 
 struct AttnWs {
   size_t counters, acc, ml, total;
@@ -140,7 +158,7 @@ AttnWs attn_ws_layout(int batch, int num_kv_heads, int rows_pad, int splits) {
 size_t attn_ws_bytes(int batch, int num_q_heads, int num_kv_heads, int nq_max, int64_t tokens) {
   if (batch <= 0 || num_kv_heads <= 0 || num_q_heads % num_kv_heads) return 0;
   const int rt = attn_row_tiles(nq_max, num_q_heads / num_kv_heads);
-  const int splits = attn_splits(batch, num_kv_heads, tokens + nq_max);
+  const int splits = attn_splits(batch, num_kv_heads, tokens + nq_max).slots;
   return attn_ws_layout(batch, num_kv_heads, rt * 16, splits).total;
 }
 
@@ -227,13 +245,15 @@ dustin_status prepare_attention(bool sparse, const void* q, int64_t q_sb, int64_
   const int rt = attn_row_tiles(bt->nq_max, gs);
   a.rows_pad = rt * 16;
   const int64_t tokens_max = tokens + bt->nq_max;
-  a.splits = attn_splits(B, Hkv, tokens_max);
+  const AttnSplits sp = attn_splits(B, Hkv, tokens_max);
+  a.splits = sp.slots;
   const bool sep = rt <= kAttnSepMaxRT;  // the kernels give the window a step of its own there
   // 32-token steps of the longest pair that the splits share: its selected (or committed)
   // tokens, with the window's tokens as a step of their own when sep is set
   const int64_t steps_max = sep ? (tokens > 0 ? (tokens + 31) / 32 : 1) : (tokens_max + 31) / 32;
   a.split_steps = (int)((steps_max + a.splits - 1) / a.splits);
-  a.min_split_steps = env_int("DUSTIN_ATTN_SPLITS", 0) > 0 ? 1 : 8;
+  a.min_split_steps = sp.min_steps;
+  a.merge_spins = env_int("DUSTIN_ATTN_MERGE_SPINS", 1 << 14);
   call->rt = rt;
   call->paged = kv.page_table != nullptr;
   return DUSTIN_OK;

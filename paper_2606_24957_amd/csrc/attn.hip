@@ -1164,11 +1164,96 @@ __global__ __launch_bounds__(kW * kWave) void verify_attn_kernel(AttnArgs a) {
   }
   wait_vmem_all();  // this thread's write-through stores have completed
   __syncthreads();  // ... and every other thread's
+  // arrivals in the low byte, departures in the next; the mask of slices left undone (below)
+  int32_t* const count = a.counters + pair * kAttnCounterStride;
+  int32_t* const undone = count + kAttnMaskOffset;
   if (threadIdx.x == 0)
-    sm_last = __hip_atomic_fetch_add(a.counters + pair, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nsplit - 1;
+    sm_last = (__hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xff) == nsplit - 1;
   __syncthreads();
+  if (nsplit > kAttnMergeAlone) {
+    // Many splits share the merge: split i merges the i-th of nsplit slices of the rows'
+    // elements, once all have arrived.  One workgroup reads the others' partials at about
+    // 36 GB/s, 20 KB each at 40 rows: a lone sequence's 8 KV heads of 2048 tokens in eight
+    // splits took 18.8 us, in sixteen 23.3, and now 15.2 and 14.7; 8192 tokens, dense, in 32
+    // splits 38.1, now 20.5.  (With the counters of all pairs in one or two cache lines the
+    // polling of 256 workgroups cost all of that gain.)  The wait needs the pair's splits to be resident together (one
+    // launch is one round of workgroups, at most one per CU), and is bounded: a split that
+    // gives up marks its slice undone and leaves it to the last to arrive.  It marks first and
+    // looks at the count again afterwards, and the last arrives first and looks at the marks
+    // afterwards, so one of them sees the other (if both do, both write the same bits).
+    __shared__ uint32_t sm_todo;
+    if (threadIdx.x == 0) {
+      uint32_t todo = 1u << split;
+      if (sm_last) {
+        todo |= (uint32_t)__hip_atomic_load(undone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } else {
+        auto arrived = [&]() {
+          return (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xff) == nsplit;
+        };
+        bool all = false;
+        for (int spins = 0; !(all = arrived()) && spins < a.merge_spins; ++spins) __builtin_amdgcn_s_sleep(1);
+        if (!all) {
+          (void)__hip_atomic_fetch_or(undone, (int32_t)todo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          asm volatile("" ::: "memory");
+          wait_vmem_all();  // the mark is made before the count is read again
+          if (!arrived()) todo = 0u;
+        }
+      }
+      sm_todo = todo;
+    }
+    __syncthreads();
+    asm volatile("" ::: "memory");  // the partials are read only after the count is complete
+    const int acc_bytes = a.rows_pad * kD * 4, ml_bytes = a.rows_pad * 2 * 4;  // of one split
+    const auto ra = __builtin_amdgcn_make_buffer_rsrc(a.part_acc + (int64_t)slot0 * a.rows_pad * kD, 0,
+                                                      nsplit * acc_bytes, 0x00020000);
+    const auto rm = __builtin_amdgcn_make_buffer_rsrc(a.part_ml + (int64_t)slot0 * a.rows_pad * 2, 0,
+                                                      nsplit * ml_bytes, 0x00020000);
+    for (uint32_t todo = __builtin_amdgcn_readfirstlane(sm_todo); todo; todo &= todo - 1) {
+      const int slice = __builtin_ctz(todo);
+      const int e_end = (slice + 1) * nel / nsplit;
+      for (int e = slice * nel / nsplit + (int)threadIdx.x; e < e_end; e += nthreads) {
+        const int r = e / (kD / 4), c0 = (e % (kD / 4)) * 4;
+        f32x4 res = {0.f, 0.f, 0.f, 0.f};
+        float Mr = -INFINITY, Lr = 0.f;
+        constexpr int kBatch = 8;  // partials loaded at once, merged online in split order
+        for (int sp0 = 0; sp0 < nsplit; sp0 += kBatch) {
+          u32x4 x[kBatch];
+          u32x2 ml[kBatch];
+#pragma unroll
+          for (int j = 0; j < kBatch; ++j) {
+            const int sp = min(sp0 + j, nsplit - 1);
+            x[j] = __builtin_amdgcn_raw_buffer_load_b128(ra, (r * kD + c0) * 4, sp * acc_bytes, kSC1);
+            ml[j] = __builtin_amdgcn_raw_buffer_load_b64(rm, r * 8, sp * ml_bytes, kSC1);
+          }
+#pragma unroll
+          for (int j = 0; j < kBatch; ++j) {
+            if (sp0 + j < nsplit) {
+              const float ms = __uint_as_float(ml[j][0]), ls = __uint_as_float(ml[j][1]);
+              const float M = fmaxf(Mr, ms), Mu = M == -INFINITY ? 0.f : M;
+              const float fa = Mr == -INFINITY ? 0.f : fast_exp2(Mr - Mu);
+              const float fb = ms == -INFINITY ? 0.f : fast_exp2(ms - Mu);
+              res = res * fa + __builtin_bit_cast(f32x4, x[j]) * fb;
+              Lr = Lr * fa + ls * fb;
+              Mr = M;
+            }
+          }
+        }
+        const f32x4 v = res * (Lr > 0.f ? 1.f / Lr : 0.f);
+        *reinterpret_cast<u32x2*>(out_ptr(r) + c0) = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
+      }
+    }
+    // the last to leave returns the counters to zero (every split arrives before it leaves, and
+    // reads the count and the marks before)
+    __syncthreads();
+    if (threadIdx.x == 0 &&
+        __hip_atomic_fetch_add(count, 0x100, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 8 == nsplit - 1) {
+      __hip_atomic_store(undone, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return;
+  }
   if (!sm_last) return;
-  if (threadIdx.x == 0) __hip_atomic_store(a.counters + pair, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
   // merge the splits online in split order (the same order whichever workgroup is last):
   // this workgroup's own partial from registers, every other one read back with one

@@ -28,7 +28,8 @@ struct AttnArgs {
   int32_t rows_pad;
   float* part_acc;          // [pairs * splits, rows_pad, 128], by unit  (splits > 1 only)
   float* part_ml;           // [pairs * splits, rows_pad, 2]
-  int32_t* counters;        // [pairs], zero between calls
+  int32_t* counters;        // one per kAttnCounterStride, marks from kAttnMaskOffset on; zero between calls
+  int32_t merge_spins;      // polls after which a split leaves its share of the merge to the last
 };
 
 // Row tiles (16 query rows each) up to which the attention kernel gives the verification
@@ -36,9 +37,18 @@ struct AttnArgs {
 // selected (or committed) positions.
 constexpr int kAttnSepMaxRT = 3;
 
+// Splits of a pair up to which the last to finish merges alone (16 sequences, 8 KV heads, 2048
+// tokens, two splits: 35.1 us, shared 37.5).
+constexpr int kAttnMergeAlone = 3;
+
 // Pairs the attention kernel's split balancing handles (four per lane of one wave); with
 // more pairs there is one workgroup per pair.
 constexpr int kAttnBalancePairs = 256;
+
+// int32 between the arrival counters of two pairs (each in a cache line and a memory channel of
+// its own: 256 workgroups poll and count at once), and from a counter to the pair's marks of
+// slices left undone.
+constexpr int kAttnCounterStride = 64, kAttnMaskOffset = kAttnBalancePairs * kAttnCounterStride;
 
 hipError_t launch_verify_attn(const AttnArgs& a, int rt, bool sparse, bool paged, hipStream_t stream);
 

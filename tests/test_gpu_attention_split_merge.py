@@ -1,0 +1,64 @@
+"""The shared merge of many token splits: each split merges a slice of the rows once all have
+arrived, and a split that stops waiting leaves its slice to the last one.  With a spin limit of
+one poll most splits stop waiting, and the outputs must keep their bits; either way every row
+matches the oracle and the workspace's counter region is zero again."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import paper_2606_24957_amd as D
+from paper_2606_24957_amd import workloads as W
+from tests.gpu_util import bits, check_attention, gpu_rows, scale_of
+from tests.test_gpu_attention import _random_selection, _shape
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _counters_clear():
+    key = (str(torch.device("cuda", torch.cuda.current_device())), int(torch.cuda.current_stream().cuda_stream), "attn")
+    buf = D._WS[key]
+    off = (-buf.data_ptr()) % 256
+    assert int(buf[off:off + (1 << 18)].count_nonzero()) == 0
+
+
+# four splits (the fewest that share), an odd number, one slice per row or less, the most; rows of
+# one, three, five and eight row tiles; the default rule's own counts (None) at 16 to 63 steps
+@pytest.mark.parametrize("splits,B,n,t,Hq,Hkv,k,paged", [
+    (4, 1, 1500, 5, 64, 8, 700, False), (5, 2, [1500, 90], [5, 3], 28, 4, 700, True),
+    (7, 1, 900, 1, 8, 1, 600, False), (16, 2, [2000, 1111], [9, 4], 64, 8, 900, False),
+    (32, 1, 3000, 16, 64, 8, 2000, False), (32, 1, 2500, 2, 8, 1, 1024, True),
+    (None, 1, 4000, 5, 64, 8, 512, False), (None, 1, 4000, 5, 8, 1, 480, False),
+    (None, 2, [4000, 600], [5, 5], 28, 4, 1024, True), (None, 1, 4000, 7, 64, 8, 2016, False),
+])
+def test_shared_merge(splits, B, n, t, Hq, Hkv, k, paged, monkeypatch):
+    if splits:
+        monkeypatch.setenv("DUSTIN_ATTN_SPLITS", str(splits))
+    s = _shape(B, n, t, Hq, Hkv, k, paged, seed=31, name=f"merge{splits}")
+    L = W.make_layer(s, 0, DEV)
+    seq = torch.tensor(s.seq_lens, dtype=torch.int32, device=DEV)
+    nq = torch.tensor(s.n_query, dtype=torch.int32, device=DEV)
+    idx_np, cnt_np = _random_selection(s, 1, 5, ())
+    idx, cnt = torch.from_numpy(idx_np).to(DEV), torch.from_numpy(cnt_np).to(DEV)
+    outs = {}
+    for spins in (None, 1):
+        if spins:
+            monkeypatch.setenv("DUSTIN_ATTN_MERGE_SPINS", str(spins))
+        for kind in ("sparse", "dense"):
+            out = torch.full_like(L.q, float("nan"))
+            for _ in range(2):
+                if kind == "sparse":
+                    D.sparse_verify_attn(L.q, L.k, L.v, idx, cnt, seq, n_query=nq, page_table=L.page_table, out=out)
+                else:
+                    D.dense_verify_attn(L.q, L.k, L.v, seq, n_query=nq, page_table=L.page_table, out=out)
+            torch.cuda.synchronize()
+            _counters_clear()
+            outs[kind, spins] = out
+    kk, vv = L.contiguous_kv(s)
+    rows = O.all_rows(s.B, s.n_query, s.num_q_heads)
+    for kind in ("sparse", "dense"):
+        sel = dict(idx=idx_np, count=cnt_np) if kind == "sparse" else {}
+        ref = O.attention(bits(L.q), bits(kk), bits(vv), s.seq_lens, scale_of(s.head_dim), rows, **sel)
+        check_attention(gpu_rows(outs[kind, None], rows), ref, f"{s.name} {kind}")
+        assert torch.equal(outs[kind, None].view(torch.int16), outs[kind, 1].view(torch.int16))
