@@ -1164,15 +1164,17 @@ __global__ __launch_bounds__(kW * kWave) void verify_attn_kernel(AttnArgs a) {
   }
   wait_vmem_all();  // this thread's write-through stores have completed
   __syncthreads();  // ... and every other thread's
-  // arrivals in the low byte, departures in the next; the mask of slices left undone (below)
+  // arrivals in the low half, departures in the high one (a pair can take all of the launch's
+  // unit slots); the mask of slices left undone (below)
   int32_t* const count = a.counters + pair * kAttnCounterStride;
   int32_t* const undone = count + kAttnMaskOffset;
   if (threadIdx.x == 0)
-    sm_last = (__hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xff) == nsplit - 1;
+    sm_last = (__hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xffff) == nsplit - 1;
   __syncthreads();
   if (nsplit > kAttnMergeAlone) {
-    // Many splits share the merge: split i merges the i-th of nsplit slices of the rows'
-    // elements, once all have arrived.  One workgroup reads the others' partials at about
+    // Many splits share the merge: split i merges the i-th slice of the rows' elements, once all
+    // have arrived.  There are as many slices as splits, at most the 32 that the mask holds: the
+    // longest pairs of a ragged batch take more splits, and the others of theirs only arrive.  One workgroup reads the others' partials at about
     // 36 GB/s, 20 KB each at 40 rows: a lone sequence's 8 KV heads of 2048 tokens in eight
     // splits took 18.8 us, in sixteen 23.3, and now 15.2 and 14.7; 8192 tokens, dense, in 32
     // splits 38.1, now 20.5.  (With the counters of all pairs in one or two cache lines the
@@ -1182,13 +1184,14 @@ __global__ __launch_bounds__(kW * kWave) void verify_attn_kernel(AttnArgs a) {
     // looks at the count again afterwards, and the last arrives first and looks at the marks
     // afterwards, so one of them sees the other (if both do, both write the same bits).
     __shared__ uint32_t sm_todo;
+    const int nslices = min(nsplit, 32);
     if (threadIdx.x == 0) {
-      uint32_t todo = 1u << split;
+      uint32_t todo = split < nslices ? 1u << split : 0u;
       if (sm_last) {
         todo |= (uint32_t)__hip_atomic_load(undone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      } else {
+      } else if (todo) {
         auto arrived = [&]() {
-          return (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xff) == nsplit;
+          return (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xffff) == nsplit;
         };
         bool all = false;
         for (int spins = 0; !(all = arrived()) && spins < a.merge_spins; ++spins) __builtin_amdgcn_s_sleep(1);
@@ -1210,8 +1213,8 @@ __global__ __launch_bounds__(kW * kWave) void verify_attn_kernel(AttnArgs a) {
                                                       nsplit * ml_bytes, 0x00020000);
     for (uint32_t todo = __builtin_amdgcn_readfirstlane(sm_todo); todo; todo &= todo - 1) {
       const int slice = __builtin_ctz(todo);
-      const int e_end = (slice + 1) * nel / nsplit;
-      for (int e = slice * nel / nsplit + (int)threadIdx.x; e < e_end; e += nthreads) {
+      const int e_end = (slice + 1) * nel / nslices;
+      for (int e = slice * nel / nslices + (int)threadIdx.x; e < e_end; e += nthreads) {
         const int r = e / (kD / 4), c0 = (e % (kD / 4)) * 4;
         f32x4 res = {0.f, 0.f, 0.f, 0.f};
         float Mr = -INFINITY, Lr = 0.f;
@@ -1246,7 +1249,7 @@ __global__ __launch_bounds__(kW * kWave) void verify_attn_kernel(AttnArgs a) {
     // reads the count and the marks before)
     __syncthreads();
     if (threadIdx.x == 0 &&
-        __hip_atomic_fetch_add(count, 0x100, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 8 == nsplit - 1) {
+        __hip_atomic_fetch_add(count, 0x10000, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16 == nsplit - 1) {
       __hip_atomic_store(undone, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }

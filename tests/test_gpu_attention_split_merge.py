@@ -62,3 +62,27 @@ def test_shared_merge(splits, B, n, t, Hq, Hkv, k, paged, monkeypatch):
         ref = O.attention(bits(L.q), bits(kk), bits(vv), s.seq_lens, scale_of(s.head_dim), rows, **sel)
         check_attention(gpu_rows(outs[kind, None], rows), ref, f"{s.name} {kind}")
         assert torch.equal(outs[kind, None].view(torch.int16), outs[kind, 1].view(torch.int16))
+
+
+# one long sequence among short or empty ones: its pairs take more splits than the merge has slices
+# (some 60, some 160, and where an empty pair has no step, with four row tiles, all 256)
+@pytest.mark.parametrize("Hq,Hkv,n,t", [
+    (32, 4, [16000, 90], [5, 3]), (8, 1, [20000] + [40] * 7, [5] * 8), (4, 1, [32752] + [0] * 7, [16] + [0] * 7),
+])
+@pytest.mark.parametrize("spins", [None, 1])
+def test_more_splits_than_slices(Hq, Hkv, n, t, spins, monkeypatch):
+    if spins:
+        monkeypatch.setenv("DUSTIN_ATTN_MERGE_SPINS", str(spins))
+    g = torch.Generator(device=DEV).manual_seed(5)
+    B, N, T = len(n), max(n) + max(t), max(t)
+    q = torch.randn(B, T, Hq, 128, device=DEV, dtype=torch.bfloat16, generator=g)
+    k, v = (torch.randn(B, N, Hkv, 128, device=DEV, dtype=torch.bfloat16, generator=g) for _ in range(2))
+    seq, nq = (torch.tensor(x, dtype=torch.int32, device=DEV) for x in (n, t))
+    out = torch.full_like(q, float("nan"))
+    for _ in range(2):
+        D.dense_verify_attn(q, k, v, seq, n_query=nq, out=out)
+    torch.cuda.synchronize()
+    _counters_clear()
+    rows = O.all_rows(B, t, Hq)
+    ref = O.attention(bits(q), bits(k), bits(v), n, scale_of(128), rows)
+    check_attention(gpu_rows(out, rows), ref, f"{Hq}/{Hkv} {n}")
