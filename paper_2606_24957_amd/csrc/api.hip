@@ -96,12 +96,12 @@ int attn_row_tiles(int nq_max, int group_size) {
   return rt < 1 ? 1 : rt;
 }
 
-// The token splits of a launch: unit slots per (b, g) on average, and the smallest split, in steps
-// of 32 tokens, that the kernel's balancing may choose.  It sizes the splits from the actual
-// per-pair lengths, so that longer pairs take more of the slots; beyond kAttnBalancePairs
-// pairs each pair is one workgroup.
+// The token splits of a launch: splits of each pair when all are equally long, unit slots of the
+// launch, and the smallest split, in steps of 32 tokens, that the kernel's balancing may choose.
+// It sizes the splits from the actual per-pair lengths, so that longer pairs take more of the
+// slots; beyond kAttnBalancePairs pairs each pair is one workgroup.
 struct AttnSplits {
-  int slots, min_steps;
+  int splits, units, min_steps;
 };
 
 // As many workgroups as the chip holds in one round (256 CUs, one workgroup of four waves
@@ -115,7 +115,7 @@ struct AttnSplits {
 // two 13.9.
 AttnSplits attn_splits(int batch, int num_kv_heads, int64_t tokens_per_pair) {
   const int64_t pairs = (int64_t)batch * num_kv_heads;
-  if (pairs <= 0 || pairs > kAttnBalancePairs) return {1, 8};
+  if (pairs <= 0 || pairs > kAttnBalancePairs) return {1, (int)(pairs > 0 ? pairs : 1), 8};
   const int64_t steps = (tokens_per_pair + 31) / 32;
   int64_t s, min_steps = 8;
   const int forced = env_int("DUSTIN_ATTN_SPLITS", 0);
@@ -131,7 +131,10 @@ AttnSplits attn_splits(int batch, int num_kv_heads, int64_t tokens_per_pair) {
   }
   if (s > kAttnMaxSplits) s = kAttnMaxSplits;
   if (s > steps) s = steps;
-  return {s < 1 ? 1 : (int)s, (int)min_steps};
+  if (s < 1) s = 1;
+  // pairs that do not divide the CUs leave slots over, for the longer pairs of a ragged batch
+  const bool all = forced <= 0 && s > 1 && s == kAttnBalancePairs / pairs;
+  return {(int)s, (int)(all ? kAttnBalancePairs : pairs * s), (int)min_steps};
 }
 
 // Split workspace: a fixed counter region first (the arrival counters and marks of up to
@@ -144,13 +147,12 @@ struct AttnWs {
   size_t counters, acc, ml, total;
 };
 
-AttnWs attn_ws_layout(int batch, int num_kv_heads, int rows_pad, int splits) {
+AttnWs attn_ws_layout(int rows_pad, const AttnSplits& sp) {
   AttnWs w{0, 0, 0, 0};
-  if (splits <= 1) return w;
-  const size_t pairs = (size_t)batch * num_kv_heads;
+  if (sp.splits <= 1) return w;
   w.counters = kAttnMaxPairs * sizeof(int32_t);
-  w.acc = round_up(pairs * splits * rows_pad * 128 * sizeof(float), kAlign);
-  w.ml = round_up(pairs * splits * rows_pad * 2 * sizeof(float), kAlign);
+  w.acc = round_up((size_t)sp.units * rows_pad * 128 * sizeof(float), kAlign);
+  w.ml = round_up((size_t)sp.units * rows_pad * 2 * sizeof(float), kAlign);
   w.total = w.counters + w.acc + w.ml;
   return w;
 }
@@ -158,8 +160,7 @@ AttnWs attn_ws_layout(int batch, int num_kv_heads, int rows_pad, int splits) {
 size_t attn_ws_bytes(int batch, int num_q_heads, int num_kv_heads, int nq_max, int64_t tokens) {
   if (batch <= 0 || num_kv_heads <= 0 || num_q_heads % num_kv_heads) return 0;
   const int rt = attn_row_tiles(nq_max, num_q_heads / num_kv_heads);
-  const int splits = attn_splits(batch, num_kv_heads, tokens + nq_max).slots;
-  return attn_ws_layout(batch, num_kv_heads, rt * 16, splits).total;
+  return attn_ws_layout(rt * 16, attn_splits(batch, num_kv_heads, tokens + nq_max)).total;
 }
 
 // A validated attention call: its kernel arguments (workspace fields still unset), the row
@@ -246,7 +247,8 @@ dustin_status prepare_attention(bool sparse, const void* q, int64_t q_sb, int64_
   a.rows_pad = rt * 16;
   const int64_t tokens_max = tokens + bt->nq_max;
   const AttnSplits sp = attn_splits(B, Hkv, tokens_max);
-  a.splits = sp.slots;
+  a.splits = sp.splits;
+  a.units = sp.units;
   const bool sep = rt <= kAttnSepMaxRT;  // the kernels give the window a step of its own there
   // 32-token steps of the longest pair that the splits share: its selected (or committed)
   // tokens, with the window's tokens as a step of their own when sep is set
@@ -263,7 +265,7 @@ dustin_status prepare_attention(bool sparse, const void* q, int64_t q_sb, int64_
 dustin_status launch_attention(AttnCall& call, bool sparse, void* ws, void* stream) {
   AttnArgs& a = call.a;
   if (a.splits > 1) {
-    const AttnWs w = attn_ws_layout(a.pairs / a.num_kv_heads, a.num_kv_heads, a.rows_pad, a.splits);
+    const AttnWs w = attn_ws_layout(a.rows_pad, AttnSplits{a.splits, a.units, a.min_split_steps});
     char* base = static_cast<char*>(ws);
     a.counters = reinterpret_cast<int32_t*>(base);
     a.part_acc = reinterpret_cast<float*>(base + w.counters);

@@ -191,19 +191,19 @@ __global__ __launch_bounds__(kW * kWave) void verify_attn_kernel(AttnArgs a) {
   asm volatile("" ::"s"(a.q), "s"(a.q_sb), "s"(a.q_st), "s"(a.q_sh), "s"(a.idx), "s"(a.idx_sb),
                "s"(a.idx_sg), "s"(a.count), "s"(a.dims.seq_lens), "s"(a.dims.n_query),
                "s"(a.dims.max_len), "s"(a.dims.nq_max), "s"(a.dims.k_max), "s"(a.groups),
-               "s"(a.num_kv_heads), "s"(a.group_size), "s"(a.pairs), "s"(a.splits),
+               "s"(a.num_kv_heads), "s"(a.group_size), "s"(a.pairs), "s"(a.splits), "s"(a.units),
                "s"(a.split_steps), "s"(a.min_split_steps));
   asm volatile("" ::"s"(a.k.data), "s"(a.k.stride_b), "s"(a.k.stride_n), "s"(a.k.stride_h),
                "s"(a.k.capacity), "s"(a.v.data), "s"(a.v.stride_b), "s"(a.v.stride_n), "s"(a.v.stride_h),
                "s"(a.out), "s"(a.counters), "s"(a.part_acc), "s"(a.part_ml), "s"(a.rows_pad),
                "s"(a.scale_log2));
 
-  // ---- which (pair, split) this workgroup runs.  The grid holds U = pairs * splits unit
-  // slots; XCD x (blockIdx % 8) runs units ceil(x A / 8) .. ceil((x + 1) A / 8) - 1 of the A
+  // ---- which (pair, split) this workgroup runs.  The grid holds U unit slots;
+  // XCD x (blockIdx % 8) runs units ceil(x A / 8) .. ceil((x + 1) A / 8) - 1 of the A
   // units there are, a contiguous run, so that the splits of a pair and the KV heads of a
   // sequence share an XCD (its L2 and its address translations).
   const int xcd = blockIdx.x & 7, xslot = blockIdx.x >> 3;
-  const int U = a.pairs * a.splits;
+  const int U = a.units;
   auto unit_of = [&](int A, int& unit) {
     unit = (xcd * A + 7) / 8 + xslot;
     return unit < ((xcd + 1) * A + 7) / 8;
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(kW * kWave) void verify_attn_kernel(AttnArgs a) {
   // already in flight; they are issued again only if the guess was wrong.
   const bool balance = a.splits > 1;  // kernel-uniform
   int unit = 0;
-  const bool guess_ok = unit_of(U, unit);
+  const bool guess_ok = unit_of(a.pairs * a.splits, unit);
   int pair = guess_ok ? unit / a.splits : 0;
   int split = unit - pair * a.splits;
   int s_begin = split * a.split_steps;
@@ -1309,8 +1309,7 @@ __global__ __launch_bounds__(kW * kWave) void verify_attn_kernel(AttnArgs a) {
 
 template <int RT, bool kSparse, bool kPaged>
 static hipError_t launch_rt(const AttnArgs& a, hipStream_t stream) {
-  const int units = a.splits * a.pairs;
-  const int blocks = (units + 7) / 8 * 8;
+  const int blocks = (a.units + 7) / 8 * 8;
   constexpr bool kQReg = RT <= 3;
   hipLaunchKernelGGL((verify_attn_kernel<RT, kSparse, kPaged, kQReg>), dim3(blocks), dim3(kW * kWave), 0,
                      stream, a);

@@ -22,12 +22,13 @@ struct AttnArgs {
   int32_t num_kv_heads, group_size;
   int32_t pairs;        // B * num_kv_heads
   float scale_log2;
-  int32_t splits;           // unit slots per (b, g) on average: the grid holds pairs * splits
+  int32_t splits;           // splits of each pair when all are equally long
+  int32_t units;            // unit slots of the launch, at least pairs * splits
   int32_t split_steps;      // 32-token steps per split when every pair is as long as the longest
   int32_t min_split_steps;  // smallest split the kernel's balancing may choose
   int32_t rows_pad;
-  float* part_acc;          // [pairs * splits, rows_pad, 128], by unit  (splits > 1 only)
-  float* part_ml;           // [pairs * splits, rows_pad, 2]
+  float* part_acc;          // [units, rows_pad, 128], by unit  (splits > 1 only)
+  float* part_ml;           // [units, rows_pad, 2]
   int32_t* counters;        // one per kAttnCounterStride, marks from kAttnMaskOffset on; zero between calls
   int32_t merge_spins;      // polls after which a split leaves its share of the merge to the last
 };
