@@ -9,22 +9,21 @@ namespace dustin {
 
 constexpr int kKvThreads = 256;
 
-// One 16-byte chunk per thread; rows are (cache: K then V, sequence, token, KV head).
-__global__ __launch_bounds__(kKvThreads) void kv_append_kernel(KvAppendArgs a) {
-  const int cpr = a.head_dim / 8;  // chunks per row
-  int64_t i = (int64_t)blockIdx.x * kKvThreads + threadIdx.x;
-  const int chunk = (int)(i % cpr);
-  i /= cpr;
-  const int h = (int)(i % a.num_kv_heads);
-  i /= a.num_kv_heads;
-  const int t = (int)(i % a.dims.nq_max);
-  i /= a.dims.nq_max;
-  const int b = (int)(i % a.batch);
-  const int which = (int)(i / a.batch);
-  if (which >= 2) return;
-  if (t >= a.dims.nq(b)) return;
-  const int64_t pos = (int64_t)a.dims.len(b) + t;
-  const KvView& c = which == 0 ? a.k : a.v;
+// One 16-byte chunk per thread; a workgroup belongs to one cache (K or V) and one sequence, whose
+// lengths are scalar loads that run beside the threads' (token, KV head, chunk) arithmetic.
+// Bound by its chain of loads (lengths, page, row).
+__global__ __launch_bounds__(kKvThreads) void kv_append_kernel(KvAppendArgs a, uint32_t parts, int b0) {
+  const bool is_v = blockIdx.x & 1;
+  const uint32_t seq = (blockIdx.x >> 1) / parts, part = (blockIdx.x >> 1) - seq * parts;
+  const int b = b0 + (int)seq;
+  const int T = a.dims.nq(b), N = a.dims.len(b);
+  const uint32_t cpr = (uint32_t)a.head_dim / 8, heads = (uint32_t)a.num_kv_heads;  // chunks per row
+  const uint32_t i = part * kKvThreads + threadIdx.x;
+  const uint32_t r = i / cpr, chunk = i - r * cpr;
+  const uint32_t t = r / heads, h = r - t * heads;
+  if (t >= (uint32_t)T) return;
+  const int64_t pos = (int64_t)N + t;
+  const KvView& c = is_v ? a.v : a.k;
   int64_t row;
   if (c.page_table) {
     const int64_t slot = pos >> c.page_shift;
@@ -35,17 +34,23 @@ __global__ __launch_bounds__(kKvThreads) void kv_append_kernel(KvAppendArgs a) {
     if (pos >= c.capacity) return;
     row = (int64_t)b * c.stride_b + pos * c.stride_n;
   }
-  const uint16_t* src = (which == 0 ? a.k_new : a.v_new) + (int64_t)b * (which == 0 ? a.k_sb : a.v_sb) +
-                        (int64_t)t * (which == 0 ? a.k_st : a.v_st) + (int64_t)h * (which == 0 ? a.k_sh : a.v_sh);
+  const uint16_t* src = (is_v ? a.v_new : a.k_new) + (int64_t)b * (is_v ? a.v_sb : a.k_sb) +
+                        (int64_t)t * (is_v ? a.v_st : a.k_st) + (int64_t)h * (is_v ? a.v_sh : a.k_sh);
   uint16_t* dst = const_cast<uint16_t*>(c.data) + row + (int64_t)h * c.stride_h;
   *reinterpret_cast<u32x4*>(dst + 8 * chunk) = *reinterpret_cast<const u32x4*>(src + 8 * chunk);
 }
 
 hipError_t launch_kv_append(const KvAppendArgs& a, hipStream_t stream) {
-  const int64_t threads = 2 * (int64_t)a.batch * a.dims.nq_max * a.num_kv_heads * (a.head_dim / 8);
-  if (threads == 0) return hipSuccess;
-  const int64_t blocks = (threads + kKvThreads - 1) / kKvThreads;
-  hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)blocks), dim3(kKvThreads), 0, stream, a);
+  const int64_t chunks = (int64_t)a.dims.nq_max * a.num_kv_heads * (a.head_dim / 8);  // of one sequence
+  if (a.batch == 0 || chunks == 0) return hipSuccess;
+  const int64_t parts = (chunks + kKvThreads - 1) / kKvThreads;
+  const int64_t most = ((INT64_C(1) << 32) / kKvThreads - 1) / (2 * parts);  // sequences: a grid has less than 2^32 threads
+  if (most < 1) return hipErrorInvalidValue;
+  for (int64_t b0 = 0; b0 < a.batch; b0 += most) {
+    const int64_t n = a.batch - b0 < most ? a.batch - b0 : most;
+    hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)(2 * n * parts)), dim3(kKvThreads), 0, stream, a,
+                       (uint32_t)parts, (int)b0);
+  }
   return hipGetLastError();
 }
 
