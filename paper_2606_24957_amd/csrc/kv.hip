@@ -11,7 +11,8 @@ constexpr int kKvThreads = 256;
 
 // One 16-byte chunk per thread; a workgroup belongs to one cache (K or V) and one sequence, whose
 // lengths are scalar loads that run beside the threads' (token, KV head, chunk) arithmetic.
-// Bound by its chain of loads (lengths, page, row).
+// Bound by its launch and chain of loads (lengths, page, row): with the row found by 64-bit divisions,
+// 3.9 to 4.8 us a launch for one sequence, 5 rows of 8 KV heads, about 0.5 us more than now.
 __global__ __launch_bounds__(kKvThreads) void kv_append_kernel(KvAppendArgs a, uint32_t parts, int b0) {
   const bool is_v = blockIdx.x & 1;
   const uint32_t seq = (blockIdx.x >> 1) / parts, part = (blockIdx.x >> 1) - seq * parts;

@@ -38,6 +38,20 @@ def test_kv_append_contiguous(strided):
     np.testing.assert_array_equal(bits(v), O.kv_append(vb, bits(v_new), seq, nq))
 
 
+@pytest.mark.parametrize("H,d,T", [(1, 64, 1), (3, 64, 16), (40, 128, 16)])
+def test_kv_append_parts(H, d, T):
+    """One chunk row, two workgroups with a part-filled one, and forty per cache and sequence."""
+    B, cap = 3, 40
+    k, v = _rand_bf16((B, cap, H, d), 21), _rand_bf16((B, cap, H, d), 22)
+    k_new, v_new = _rand_bf16((B, T, H, d), 23), _rand_bf16((B, T, H, d), 24)
+    seq = [0, 11, cap - T]
+    kb, vb = bits(k), bits(v)
+    D.kv_append(k_new, v_new, k, v, torch.tensor(seq, dtype=torch.int32, device=DEV), max_len=cap - T)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(bits(k), O.kv_append(kb, bits(k_new), seq, [T] * B))
+    np.testing.assert_array_equal(bits(v), O.kv_append(vb, bits(v_new), seq, [T] * B))
+
+
 def test_kv_append_paged():
     B, ps, H, d, T, maxp = 4, 16, 2, 128, 9, 12
     rng = np.random.default_rng(6)
