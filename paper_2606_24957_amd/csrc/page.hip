@@ -15,12 +15,15 @@
 namespace dustin {
 
 constexpr int kMetaThreads = 256;
-constexpr int kMetaBatch = 8;  // positions loaded together
+// Positions loaded together: a whole page of 16, so that the few threads of a refresh wait for one
+// round of loads instead of three (16 sequences, 8 KV heads: 6.0 -> 5.1 us), or 8 where pages are
+// smaller.
+constexpr int kMetaBatch = 16, kMetaBatchSmall = 8;
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-template <int D, bool kPaged>
+template <int D, bool kPaged, int kBatch>
 __global__ __launch_bounds__(kMetaThreads) void page_meta_kernel(PageMetaArgs a) {
   constexpr int C = D / 8;  // 16-byte chunks per row
   constexpr int kPagesPerBlock = kMetaThreads / C;
@@ -35,13 +38,13 @@ __global__ __launch_bounds__(kMetaThreads) void page_meta_kernel(PageMetaArgs a)
 
   const u32x4 first = load16(a.k.row<kPaged>(b, n0, g) + 8 * c);
   u32x4 hi = first, lo = first;  // bf16 pairs; halves updated independently
-  for (int n = n0 + 1; n < n1; n += kMetaBatch) {
-    u32x4 r[kMetaBatch];
+  for (int n = n0; n < n1; n += kBatch) {
+    u32x4 r[kBatch];
 #pragma unroll
-    for (int u = 0; u < kMetaBatch; ++u)  // past the page: the first row again (never replaces)
-      r[u] = n + u < n1 ? load16(a.k.row<kPaged>(b, n + u, g) + 8 * c) : first;
+    for (int u = 0; u < kBatch; ++u)  // past the page: its last row again (a repeated row never replaces)
+      r[u] = load16(a.k.row<kPaged>(b, min(n + u, n1 - 1), g) + 8 * c);
 #pragma unroll
-    for (int u = 0; u < kMetaBatch; ++u) {
+    for (int u = 0; u < kBatch; ++u) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const uint32_t x = r[u][i];
@@ -59,16 +62,24 @@ __global__ __launch_bounds__(kMetaThreads) void page_meta_kernel(PageMetaArgs a)
   *reinterpret_cast<u32x4*>(row + D) = lo;
 }
 
+template <int D, bool kPaged>
+static void launch_meta(const PageMetaArgs& a, dim3 grid, hipStream_t stream) {
+  if ((1 << a.page_shift) >= kMetaBatch)
+    hipLaunchKernelGGL((page_meta_kernel<D, kPaged, kMetaBatch>), grid, dim3(kMetaThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL((page_meta_kernel<D, kPaged, kMetaBatchSmall>), grid, dim3(kMetaThreads), 0, stream, a);
+}
+
 hipError_t launch_page_meta(const PageMetaArgs& a, int B, int head_dim, hipStream_t stream) {
   const int ppb = kMetaThreads / (head_dim / 8);
   const dim3 grid((a.span_pages + ppb - 1) / ppb, a.num_kv_heads, B);
   const bool paged = a.k.page_table != nullptr;
   if (head_dim == 128) {
-    if (paged) hipLaunchKernelGGL((page_meta_kernel<128, true>), grid, dim3(kMetaThreads), 0, stream, a);
-    else hipLaunchKernelGGL((page_meta_kernel<128, false>), grid, dim3(kMetaThreads), 0, stream, a);
+    if (paged) launch_meta<128, true>(a, grid, stream);
+    else launch_meta<128, false>(a, grid, stream);
   } else if (head_dim == 64) {
-    if (paged) hipLaunchKernelGGL((page_meta_kernel<64, true>), grid, dim3(kMetaThreads), 0, stream, a);
-    else hipLaunchKernelGGL((page_meta_kernel<64, false>), grid, dim3(kMetaThreads), 0, stream, a);
+    if (paged) launch_meta<64, true>(a, grid, stream);
+    else launch_meta<64, false>(a, grid, stream);
   } else {
     return hipErrorInvalidValue;
   }

@@ -45,6 +45,18 @@ def test_page_meta_bit_exact(d, ps, seq):
         assert not got[b, P:].any()              # pages past N_b stay as they were (zero)
 
 
+@pytest.mark.parametrize("ps", [2, 8, 16, 32])
+def test_page_meta_batches_of_rows(ps):
+    """Pages of less than a batch of loads, of one and of two, the last page of every fill."""
+    seq = list(range(3 * ps + 1, 4 * ps + 1))
+    N = 4 * ps
+    k = _k(len(seq), N, 1, 128, 11, seq)
+    meta = D.page_meta(k, seq, ps, max_len=N)
+    torch.cuda.synchronize()
+    ref = O.page_meta(bits(k), seq, ps, num_pages=meta.shape[1])
+    np.testing.assert_array_equal(_meta_host(meta), ref)
+
+
 def test_page_meta_paged_cache_matches_contiguous():
     B, Hkv, d, ps, N = 3, 2, 128, 16, 700
     seq = [700, 300, 31]
@@ -122,6 +134,13 @@ def test_page_score_all_heads_target_shape():
     heads, 5 verification queries: 40 pairs per KV head, three column tiles)."""
     _score_case(2, [3000, 1234], [5, 3], 64, 8, 128, list(range(64)), 16, with_init=False)
     _score_case(2, [3000, 1234], [5, 3], 64, 8, 128, list(range(64)), 16, seed=1)
+
+
+@pytest.mark.parametrize("n", [10752, 10754, 11300])
+def test_page_score_longer_chunks(n):
+    """Two-position pages of three sequences, 8 KV heads of 18 pairs (two column tiles each): 504
+    workgroups of 256 pages, and 528 and 552, which become chunks of 512 (the last with one page)."""
+    _score_case(3, [n, 1026, 41], [9, 4, 9], 16, 8, 64, list(range(16)), 2, seed=3)
 
 
 def test_page_score_scoring_heads_per_group_and_draft_shape():
