@@ -907,6 +907,22 @@ dustin_status dustin_page_meta(const dustin_kv* k, const dustin_batch* bt, const
   return e == hipSuccess ? DUSTIN_OK : DUSTIN_ERR_LAUNCH;
 }
 
+namespace {
+
+// Pages per pass-1 workgroup of the page score: 256, or 512 where several column tiles share a
+// workgroup (two fit a CU) and workgroups of 256 pages would need more than one round of the
+// chip: each then loads its query operands half as often, and the finish merges half the
+// statistics.  Measured, 256 against 512 pages, all heads, 16-position pages: 16 x 32768 (64 query
+// heads) 54.7 -> 51.4 us, 12 x 30001 48.7 -> 45.1, 4 x 131072 48.1 -> 43.7, 8 x 65536 with 9
+// queries 92.7 -> 83.6; in one round 256 is better: 8 x 32768 33.6, 512 34.1; 1 x 131072 26.9, 31.6;
+// 3 x 5000 17.8, 19.4.  1024 pages: 16 x 32768 6 us slower than 512.
+int32_t score_page_chunk(int64_t B, int n_groups, int max_group, int32_t pages) {
+  const int64_t blocks = B * n_groups * ((pages + kScorePageChunk - 1) / kScorePageChunk);
+  return max_group > 1 && blocks > 2 * kScoreSyncCUs ? 2 * kScorePageChunk : kScorePageChunk;
+}
+
+}  // namespace
+
 size_t dustin_page_score_workspace(int32_t batch, int32_t max_len, int32_t page_size, int32_t nq_max,
                                    int32_t n_heads) {
   if (batch <= 0 || max_len <= 0 || nq_max <= 0 || n_heads <= 0 || !page_size_ok(page_size)) return 0;
@@ -952,7 +968,9 @@ dustin_status dustin_page_score(const void* q, int64_t q_sb, int64_t q_sj, int64
   a.dims = dims_of(bt);
   a.page_mode = 1;
   a.page_shift = log2_exact(page_size);
-  a.chunk = kScorePageChunk;
+  a.chunk = score_page_chunk(B, n_groups, max_group, P);
+  if (workspace_bytes < dustin_page_score_workspace(B, bt->max_len, page_size, bt->nq_max, n_heads))
+    return DUSTIN_ERR_WORKSPACE;
   sp.n_groups = n_groups;
   sp.max_group = max_group;
   st = score_fill(sp, 2 * head_dim, B, bt->nq_max, P, scale, groups, init, init_sb, init_sg, out, out_sb, out_sg,

@@ -55,8 +55,8 @@ hipError_t launch_verify_attn(const AttnArgs& a, int rt, bool sparse, bool paged
 
 // ---- scoring-head importance (score.hip) ----
 constexpr int kScoreWaves = 4;
-constexpr int kScoreChunk = 1024;        // positions per pass-1 workgroup (256 pages in page mode)
-constexpr int kScorePageChunk = 256;
+constexpr int kScoreChunk = 1024;        // positions per pass-1 workgroup
+constexpr int kScorePageChunk = 256;     // pages per pass-1 workgroup in page mode (or twice as many)
 constexpr int kScoreFinishChunk = 1024;  // positions per pass-2 workgroup (4 per thread)
 constexpr int kScoreFinishPages = 64;    // pages per pass-2 workgroup in page mode
 constexpr int kScoreMaxHeads = 64;
