@@ -30,8 +30,8 @@
 //          and counts itself in with an atomic add on the unit's counter; the workgroup
 //          that arrives last reads the other partials back with agent-scope loads,
 //          merges all of them in split order (deterministic whichever arrives last),
-//          writes the output and returns the counter to zero.  No workgroup waits for
-//          another and no cache is flushed.
+//          writes the output and returns the counter to zero.  From kAttnMergeAlone + 1 splits
+//          on, every split waits (bounded) for the others and merges a slice.  No cache is flushed.
 //
 // Gathered positions (sparse) and page translations (paged) are resolved into an LDS table
 // of physical rows before the token loop, so the loop does no dependent global loads.
