@@ -910,15 +910,17 @@ dustin_status dustin_page_meta(const dustin_kv* k, const dustin_batch* bt, const
 namespace {
 
 // Pages per pass-1 workgroup of the page score: 256, or 512 where several column tiles share a
-// workgroup (two fit a CU) and workgroups of 256 pages would need more than one round of the
-// chip: each then loads its query operands half as often, and the finish merges half the
-// statistics.  Measured, 256 against 512 pages, all heads, 16-position pages: 16 x 32768 (64 query
-// heads) 54.7 -> 51.4 us, 12 x 30001 48.7 -> 45.1, 4 x 131072 48.1 -> 43.7, 8 x 65536 with 9
-// queries 92.7 -> 83.6; in one round 256 is better: 8 x 32768 33.6, 512 34.1; 1 x 131072 26.9, 31.6;
-// 3 x 5000 17.8, 19.4.  1024 pages: 16 x 32768 6 us slower than 512.
+// workgroup (two fit a CU) and workgroups of 256 pages would need two rounds of the chip: each then
+// loads its query operands half as often, and the finish merges half the statistics.  Measured,
+// 256 against 512 pages, all heads, 16-position pages: 16 x 32768 (64 query heads) 54.7 -> 51.4 us,
+// 4 x 131072 48.1 -> 43.7, 8 x 65536 with 9 queries 92.7 -> 83.6; in one round 256 is better: 8 x
+// 32768 33.6, 512 34.1; 1 x 131072 26.9, 31.6; 3 x 5000 17.8, 19.4.  1024 pages: 16 x 32768 6 us
+// slower than 512.  The line is at two rounds since the lengths of a ragged batch, about half of
+// the longest, are not known here: 7 sequences of up to 112402 (28 heads, 784 workgroups by the
+// longest) 36.6 us, 512 40.5; from 1024 on 512 wins or ties (16 of up to 65536, 28 heads, 52.8 -> 48.1).
 int32_t score_page_chunk(int64_t B, int n_groups, int max_group, int32_t pages) {
   const int64_t blocks = B * n_groups * ((pages + kScorePageChunk - 1) / kScorePageChunk);
-  return max_group > 1 && blocks > 2 * kScoreSyncCUs ? 2 * kScorePageChunk : kScorePageChunk;
+  return max_group > 1 && blocks >= 4 * kScoreSyncCUs ? 2 * kScorePageChunk : kScorePageChunk;
 }
 
 }  // namespace

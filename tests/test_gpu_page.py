@@ -136,10 +136,11 @@ def test_page_score_all_heads_target_shape():
     _score_case(2, [3000, 1234], [5, 3], 64, 8, 128, list(range(64)), 16, seed=1)
 
 
-@pytest.mark.parametrize("n", [10752, 10754, 11300])
+@pytest.mark.parametrize("n", [21504, 21506, 22600])
 def test_page_score_longer_chunks(n):
-    """Two-position pages of three sequences, 8 KV heads of 18 pairs (two column tiles each): 504
-    workgroups of 256 pages, and 528 and 552, which become chunks of 512 (the last with one page)."""
+    """Two-position pages of three sequences, 8 KV heads of 18 pairs (two column tiles each):
+    1008 workgroups of 256 pages, and 1032 and 1080, which become chunks of 512 (the last of the
+    first's with one page)."""
     _score_case(3, [n, 1026, 41], [9, 4, 9], 16, 8, 64, list(range(16)), 2, seed=3)
 
 
