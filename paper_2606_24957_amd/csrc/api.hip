@@ -456,7 +456,7 @@ bool score_chunk_call(const ScoreArgs& a, int32_t n_heads, int32_t nq_max, int r
     }
   }
   for (int t = 0; t < kChunkMaxTiles; ++t)
-    if (cc.cols[t] == 0) cc.col_head[t * 16] = a.heads[0];  // an empty tile repeats a pair at weight zero
+    if (cc.cols[t] == 0) cc.col_head[t * 16] = a.heads[0];  // an empty tile repeats a pair, left out of the sums
   const int64_t extent = score_extent(a, cc.kv[nu - 1], row_dim);
   if (extent < 0) return false;
   for (int l = 0; l < a.n_layers; ++l) {

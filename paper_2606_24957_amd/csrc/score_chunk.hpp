@@ -148,8 +148,8 @@ struct ScoreChunk {
   }
 
   // Column lr of column tile t: (query head, query) on used KV head cu (NT = 0).  A column past
-  // the pairs, or of a query past nq_b, repeats the tile's first column (so that it holds
-  // nothing that tile's rows do not) and gets weight zero.
+  // the pairs, or of a query past nq_b, repeats the tile's first column and is left out of the
+  // sums (col_ok): with nq_b = 0, or an empty tile, that one may itself hold anything.
   __device__ __forceinline__ void columns() {
     nq = a.dims.nq(b);
     cu = 0;

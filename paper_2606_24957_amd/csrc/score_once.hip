@@ -137,34 +137,35 @@ __device__ __forceinline__ void score_once(const ChunkCall& a, int unit, int c, 
       __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
-  // exp2(x - M) / Z = exp2(x - m_group) times exp2(m_group - M) / Z
-  float2 mz[LB][CT];
-#pragma unroll
-  for (int lb = 0; lb < LB; ++lb)
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      mz[lb][ct] = lds.mz[(lb * CT + ct) * 16 + k.lr];
-      if (!k.col_ok[ct]) mz[lb][ct].y = 0.f;
-    }
+  // exp2(x - M) / Z = exp2(x - m_group) times exp2(m_group - M) / Z, over the columns that count:
+  // the others may hold anything (a query row past nq_b is the caller's padding)
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};  // lane lr: tile lr's positions 4 lg .. + 3
 #pragma unroll
   for (int g = 0; g < TW / GS; ++g) {
-    float f[LB][CT];
+    f32x4 y[GS];
 #pragma unroll
-    for (int lb = 0; lb < LB; ++lb)
+    for (int i = 0; i < GS; ++i) y[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) f[lb][ct] = fast_exp2(gm[lb][g][ct] - mz[lb][ct].x) * mz[lb][ct].y;
+    for (int ct = 0; ct < CT; ++ct) {
+      if (!k.col_ok[ct]) continue;
+#pragma unroll
+      for (int lb = 0; lb < LB; ++lb) {
+        const float2 mz = lds.mz[(lb * CT + ct) * 16 + k.lr];
+        const float mg = gm[lb][g][ct];
+        // (the group that holds the maximum has factor 1 also where that is infinite)
+        const float f = (mg == mz.x ? 1.f : fast_exp2(mg - mz.x)) * mz.y;
+#pragma unroll
+        for (int i = 0; i < GS; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[i][e] = fmaf(x[lb][g * GS + i][ct][e], f, y[i][e]);
+      }
+    }
 #pragma unroll
     for (int i = 0; i < GS; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        float y = 0.f;
-#pragma unroll
-        for (int lb = 0; lb < LB; ++lb)
-#pragma unroll
-          for (int ct = 0; ct < CT; ++ct) y = fmaf(x[lb][g * GS + i][ct][e], f[lb][ct], y);
-        y = sum_row16(y);
-        acc[e] = k.lr == g * GS + i ? y : acc[e];
+        const float w = sum_row16(y[i][e]);
+        acc[e] = k.lr == g * GS + i ? w : acc[e];
       }
   }
   k.write(acc, layer0, 0, TW);

@@ -162,23 +162,28 @@ __device__ __forceinline__ void second_kind(const ChunkCall& a, int layer0, int 
     }
     float2 mz[CT];
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      mz[ct] = lds.mz[l * NC + ct * 16 + k.lr];
-      if (!k.col_ok[ct]) mz[ct].y = 0.f;
-    }
+    for (int ct = 0; ct < CT; ++ct) mz[ct] = lds.mz[l * NC + ct * 16 + k.lr];
     // then the next layer's rows, or (past the last layer) the last three tiles again
     const bool more = l + 1 < L;
     stream_tiles(k, k.rsrc(layer0 + l), a.tw, k.rsrc(layer0 + (more ? l + 1 : l)), more ? 0 : a.tw - 3, q,
                  [&](int t0, f32x4 (&x)[GS][CT]) {
+                   f32x4 y[GS];
+#pragma unroll
+                   for (int i = 0; i < GS; ++i) y[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                   for (int ct = 0; ct < CT; ++ct) {
+                     if (!k.col_ok[ct]) continue;  // (it may hold anything: the caller's padding)
+#pragma unroll
+                     for (int i = 0; i < GS; ++i)
+#pragma unroll
+                       for (int e = 0; e < 4; ++e)
+                         y[i][e] = fmaf(fast_exp2(fmaf(x[i][ct][e], k.scale, -mz[ct].x)), mz[ct].y, y[i][e]);
+                   }
 #pragma unroll
                    for (int i = 0; i < GS; ++i)
 #pragma unroll
                      for (int e = 0; e < 4; ++e) {
-                       float w = 0.f;
-#pragma unroll
-                       for (int ct = 0; ct < CT; ++ct)
-                         w = fmaf(fast_exp2(fmaf(x[i][ct][e], k.scale, -mz[ct].x)), mz[ct].y, w);
-                       w = sum_row16(w);
+                       const float w = sum_row16(y[i][e]);
                        acc[e] += k.lr == t0 + i ? w : 0.f;
                      }
                  });

@@ -133,6 +133,50 @@ def test_k_read_twice(lens, n_layers, per_layer, page_size):
         assert np.array_equal(np.bincount(keys, minlength=4096), host(hist)[b])
 
 
+@pytest.mark.parametrize("model,n_layers,nq_max,lens", [
+    (TARGET, 1, 4, SMALL), (DRAFT, 3, 4, SMALL), (DRAFT, 3, 5, LARGE), (ALL, 1, 3, SMALL),
+    (ALL, 1, 4, [65700, 1, 1023]), (ALL, 3, 3, [65700, 300, 1023]),
+])
+def test_padding_queries_count_for_nothing(model, n_layers, nq_max, lens):
+    """Query rows past nq_b and key rows past N_b hold NaN and infinities, with nq_b of 0, 1 and
+    some: the outputs are those of the same call with zeros there, to the bit."""
+    nq = [(nq_max, 1, 0, nq_max - 1)[b % 4] for b in range(len(lens))]
+    qs, ks, _, _, seq, nqt = _inputs(model, lens, nq, n_layers, 500 + nq_max)
+    N, outs = max(lens), []
+    junk = (0.0, float("nan"), float("inf"))
+    for fill in junk:
+        for x in qs + ks:
+            for b in range(len(lens)):
+                x[b, (nq if x.shape[1] == max(nq) else lens)[b]:] = fill
+        out = torch.full((len(lens), 1, N), -5.0, device=DEV)
+        D.score_layers(qs, ks, seq, model[3], n_query=nqt, out=out, max_len=N)
+        outs.append(out)
+    torch.cuda.synchronize()
+    _sync_region_clear()
+    for b, n in enumerate(lens):
+        got = outs[0][b, 0, :n]
+        if n:  # the softmaxes sum to one
+            assert abs(float(got.double().sum()) - n_layers * nq[b] * len(model[3])) <= 1e-4 * max(1, nq[b] * len(model[3]))
+    for fill, out in zip(junk[1:], outs[1:]):
+        assert torch.equal(out, outs[0]), f"{fill} in the padding shows"
+
+
+@pytest.mark.parametrize("model,n_layers,lens", [(TARGET, 1, [1000, 40]), (DRAFT, 3, [1000, 40]), (ALL, 1, [65700, 40])])
+def test_a_key_that_is_not_finite(model, n_layers, lens):
+    """One key of infinities or NaNs: its own position is NaN, and no other (their share of a
+    softmax over it is zero)."""
+    qs, ks, _, _, seq, nqt = _inputs(model, lens, [3, 3], n_layers, 600)
+    N = max(lens)
+    for bad in (float("inf"), float("nan")):
+        for k in ks:
+            k[0, 37, :, 3] = bad
+        out = D.score_layers(qs, ks, seq, model[3], n_query=nqt, max_len=N)
+        torch.cuda.synchronize()
+        _sync_region_clear()
+        assert torch.equal(out[0, 0].isnan().nonzero().flatten().cpu(), torch.tensor([37])), bad
+        assert not out[1, 0, :lens[1]].isnan().any()
+
+
 def test_a_pair_of_small_calls_has_the_bits_of_the_separate_calls():
     """A step's target and draft calls in one launch, 17 pairs and more, both chunk sizes."""
     for lens in (SMALL, LARGE):
