@@ -611,15 +611,17 @@ void score_choose(ScorePrep& P, int row_dim, int B, int32_t nq_max, int64_t cols
 }
 
 // The launch arguments of one or two calls of score_once.hip, or of one of score_reread.hip.
-ChunkArgs score_chunk_args(const ChunkCall* c0, const ChunkCall* c1) {
+ChunkArgs score_chunk_args(const ChunkCall* c0, const ChunkCall* c1, bool reread) {
   ChunkArgs ca;
   memset(&ca, 0, sizeof ca);
   int n = 0;
   for (const ChunkCall* c : {c0, c1}) {
     if (!c) continue;
-    ca.call[n++] = *c;
     const int units = c->batch * (c->per_layer ? c->n_layers : 1);
     ca.units = units > ca.units ? units : ca.units;
+    const int stride = kScoreSyncMaxBatch / (reread ? c->batch * c->n_layers : units);
+    ca.call[n] = *c;
+    ca.call[n++].sync_stride = stride < kChunkSyncStride ? stride : kChunkSyncStride;
   }
   // the second kind's blocks come `lag` units behind the first's: about as many blocks as the
   // chip holds, so that they find their columns merged (16 x 32768 positions, 4 layers: 252 us;
@@ -674,10 +676,10 @@ dustin_status score_run(const ScorePrep& P, void* stream) {
       break;
     }
     case ScorePrep::kOnce:
-      e = launch_score_once(score_chunk_args(&P.cc, nullptr), 1, static_cast<hipStream_t>(stream));
+      e = launch_score_once(score_chunk_args(&P.cc, nullptr, false), 1, static_cast<hipStream_t>(stream));
       break;
     case ScorePrep::kReread:
-      e = launch_score_reread(score_chunk_args(&P.cc, nullptr), static_cast<hipStream_t>(stream));
+      e = launch_score_reread(score_chunk_args(&P.cc, nullptr, true), static_cast<hipStream_t>(stream));
       break;
     default:
       e = launch_score(P.a, P.B, P.n_groups, P.max_group, P.row_dim, static_cast<hipStream_t>(stream));
@@ -835,7 +837,7 @@ dustin_status dustin_score_calls(int32_t n_calls, const dustin_score_call* calls
   }
   if (both && P[0].form == ScorePrep::kOnce && score_once_pair_supported(P[0].cc, P[1].cc)) {
     const hipError_t e =
-        launch_score_once(score_chunk_args(&P[0].cc, &P[1].cc), 2, static_cast<hipStream_t>(stream));
+        launch_score_once(score_chunk_args(&P[0].cc, &P[1].cc, false), 2, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? DUSTIN_OK : DUSTIN_ERR_LAUNCH;
   }
   for (int i = 0; i < n_calls; ++i) {

@@ -158,6 +158,11 @@ hipError_t launch_score_sync_pair(const SyncArgs& a, hipStream_t stream);
 constexpr int kChunkWaves = 4;
 constexpr int kChunkMaxTW = 16;            // most 16-position tiles per wave
 constexpr int kChunkMaxOnce = 256;         // most chunks of a sequence in score_once.hip
+// Most int32 between the counters of two units: as far apart as the region allows, so that the
+// polls and counts of one unit's workgroups do not queue behind another's in a cache line and memory
+// channel (per-layer calls of 16 units of 8192 positions, 28 pairs: adjacent 26.3 us, apart 14.7;
+// score_reread.hip, 24 layers of 16 x 16384, 56 pairs: 866 us, 624).
+constexpr int kChunkSyncStride = 64;
 constexpr int kChunkMaxTiles = 4;          // most column tiles of 16 pairs
 constexpr int kChunkMaxQ = 12;             // most column tiles times layers that one output sums (score_reread.hip)
 
@@ -179,6 +184,7 @@ struct ChunkCall {
   int32_t* sync;  // the workspace's counter region (zero between calls) and timeout flag
   float scale_log2;
   int32_t batch, n_layers, per_layer, head_dim, nu, nt, tw, chunks;
+  int32_t sync_stride;  // the launcher's: int32 between two units' counters
   int32_t share_merge;  // score_once.hip: every workgroup of the call gets a slot at once
   int32_t extent;  // bytes of K rows one buffer resource covers (a sequence, or the page pool)
   int32_t kv[4];

@@ -108,8 +108,8 @@ __device__ __forceinline__ void score_once(const ChunkCall& a, int unit, int c, 
   });
   k.summarise(m, ssum);
   __syncthreads();
-  int* const cnt = a.sync + unit;
-  int* const done = a.sync + kScoreSyncMaxBatch + unit;
+  int* const cnt = a.sync + unit * a.sync_stride;
+  int* const done = a.sync + kScoreSyncMaxBatch + unit * a.sync_stride;
   float2* const stats = reinterpret_cast<float2*>(a.stats) + (int64_t)unit * (a.chunks + 1) * NC;
   if (k.wave == 0) {  // publishes and waits
     for (int col = k.lane; col < NC; col += kWave) {

@@ -26,10 +26,10 @@ namespace {
 // counters of the sync region: chunks counted in per (layer, sequence); per sequence (or unit)
 // merged layers (high half) and second-kind workgroups done (low half)
 __device__ __forceinline__ int* first_count(const ChunkCall& a, int layer, int b) {
-  return a.sync + layer * a.batch + b;
+  return a.sync + (layer * a.batch + b) * a.sync_stride;
 }
 __device__ __forceinline__ int* second_count(const ChunkCall& a, int unit) {
-  return a.sync + kScoreSyncMaxBatch + unit;
+  return a.sync + kScoreSyncMaxBatch + unit * a.sync_stride;
 }
 template <class S>
 __device__ __forceinline__ float2* layer_stats(const ChunkCall& a, int layer, int b) {
