@@ -289,6 +289,19 @@ dustin_status run_attention(bool sparse, const void* q, int64_t q_sb, int64_t q_
   return launch_attention(call, sparse, ws, stream);
 }
 
+// Layers l0 .. l0 + n - 1 of a call with per-layer outputs.
+template <class Call>
+Call score_layers_of(const Call& c, int l0, int n, int64_t out_sl) {
+  Call r = c;
+  for (int l = 0; l < n; ++l) {
+    r.q_layers[l] = c.q_layers[l0 + l];
+    r.k_layers[l] = c.k_layers[l0 + l];
+  }
+  r.out = c.out + (int64_t)l0 * out_sl;
+  r.n_layers = n;
+  return r;
+}
+
 }  // namespace
 
 extern "C" {
@@ -335,12 +348,12 @@ int64_t score_extent(const ScoreArgs& a, int last_kv, int row_dim) {
 }
 
 // The single-pass form (score_sync.hip) for a call with at most 16 (head, query) pairs over
-// at most 4 KV heads, one output group and one output (a's heads, layers, cache view, dims,
-// output and workspace fields set): fills sc and returns true, or false when the call
-// takes the two-pass form.
+// at most 4 KV heads and one output group (a's heads, layers, cache view, dims, output and
+// workspace fields set): fills sc and returns true, or false when it does not take the call.
+// With per-layer outputs it takes one layer a launch.
 bool score_sync_plan(const ScoreArgs& a, int32_t n_heads, int32_t nq_max, int row_dim, int B, int64_t max_len,
                      int32_t groups, int32_t* sync_region, size_t logits_bytes, SyncCall& sc) {
-  if (a.page_mode || a.per_layer || groups != 1 || B > kScoreSyncMaxBatch) return false;
+  if (a.page_mode || groups != 1 || B > kScoreSyncMaxBatch) return false;
   if (row_dim != 64 && row_dim != 128) return false;
   if ((int64_t)n_heads * nq_max > 16) return false;
   memset(&sc, 0, sizeof sc);
@@ -372,14 +385,14 @@ bool score_sync_plan(const ScoreArgs& a, int32_t n_heads, int32_t nq_max, int ro
   // them.  The form keeps one workgroup on a CU for the whole call, so it is taken only
   // when every chunk the sizes allow gets a CU at once (beyond that, the two-pass form's
   // many small workgroups balance the load better).
-  int tw = (int64_t)B * max_len >= (int64_t)192 * 2048 ? 8 : 2;
+  int tw = (int64_t)B * max_len >= kScoreSyncPositions ? 8 : 2;
   int64_t chunks = (max_len + 256 * tw - 1) / (256 * tw);
   if (chunks > kScoreSyncMaxChunks && tw == 2) {  // long sequences of a small batch
     tw = 8;
     chunks = (max_len + 256 * tw - 1) / (256 * tw);
   }
   if (chunks > kScoreSyncMaxChunks || (int64_t)B * chunks > kScoreSyncCUs) return false;
-  if ((size_t)a.n_layers * B * chunks * 16 * 2 * sizeof(float) > logits_bytes) return false;
+  if ((size_t)chunks * 16 * 2 * sizeof(float) > logits_bytes) return false;
   const int64_t extent = score_extent(a, sc.kv[nu - 1], row_dim);
   if (extent < 0) return false;
   for (int l = 0; l < a.n_layers; ++l) {
@@ -554,43 +567,50 @@ struct ScorePrep {
 };
 
 // The form of a call whose two-pass arguments P.a are filled, for `cols` positions at most.
-// MI355X, 4 + 3 layers' calls of a step at the Qwen2.5-72B shape unless said otherwise:
+// MI355X; "target": one layer, 4 pairs over 4 KV heads of 128-element rows; "draft": 16 pairs over 2 KV
+// heads of 64-element rows, three layers unless said otherwise:
 //   single pass, 16-wave workgroups (score_sync.hip): at most 16 pairs, from 393216 positions of
-//     all sequences on while the chunks of 2048 fit the chip in one round.
-//   single pass, small calls (score_once.hip): a target call up to one 512-position chunk per CU
-//     (131072 positions: 38 us against 44 in two passes; past them a second workgroup on some
-//     CUs makes it 51 against 43); a draft's three layers up to two (262144: 61 us against 69),
-//     and with 17 to 32 pairs, whose logits make two passes longer, up to four (8 x 65536, 24
+//     all sequences on while the chunks of 2048 fit the chip in one round; per-layer outputs one layer
+//     a launch (16 layers of 16 x 32768, draft: 676 us, two passes 678).  Also smaller calls of summed
+//     layers that the next form does not take.
+//   single pass, small calls (score_once.hip): one layer up to one 512-position chunk per CU and 65536
+//     positions of a sequence (target of 4 x 32768: 31 us, two passes 30, a launch less; draft's layer
+//     13 against 23; a sequence of 131072 in 16 per-layer outputs 250 us, two passes 178); a draft's
+//     three layers up to two chunks per CU (8 x 32768: 43 us against 60; with at most four pairs, whose
+//     logits are few, up to one: 5 x 32768 39 us against 34), and with 17 to 32 pairs, whose logits
+//     make two passes longer, up to four (8 x 65536, 24
 //     pairs: 127 us against 155; past them a ragged batch has several rounds of workgroups
-//     of sequences that end apart, 177 us against 164 at 16 x up to 62922).  Chunks of 256 positions fill the chip better
-//     up to 32768 positions (both calls 21 us against 24), those of 512 beyond.  Per-layer
-//     outputs and single layers of more than 16 pairs, whose count of layers must not decide
-//     (a layer has the same bits in a call of its own): up to 8192 positions.
-//   K read twice (score_reread.hip): 33 to 64 pairs from 131072 positions on (24 layers of
-//     16 x 32768: 1180 us against 2020).
+//     of sequences that end apart, 177 us against 164 at 16 x up to 62922).  Chunks of 256 positions fill
+//     the chip better up to 32768 positions (target and draft 21 us against 24), those of 512 beyond.
+//     Single layers of more than 16 pairs: up to 8192 positions.
+//   K read twice (score_reread.hip): 33 to 64 pairs from 131072 positions on, below 48 pairs from
+//     262144 (16 layers of 4 x 32768, 56 pairs: 210 us, two passes 366; 4 layers of 16 x up to 8192, 36
+//     pairs: 52 us against 44).
 //   two passes (score.hip): everything else.
-void score_choose(ScorePrep& P, int row_dim, int B, int32_t nq_max, int64_t cols, int32_t groups, int32_t* sync_region,
-                  size_t logits_bytes) {
+void score_choose(ScorePrep& P, int row_dim, int B, int32_t nq_max, int64_t cols, int32_t groups, int32_t* sync_region) {
   const ScoreArgs& a = P.a;
+  // Layers that one output sums.  Nothing below may depend on the count of per-layer outputs:
+  // a layer has the same bits in a call of its own.
+  const int L = a.per_layer ? 1 : a.n_layers;
+  const size_t logits_bytes = (size_t)a.n_heads * nq_max * a.ld * sizeof(float);  // of a layer and sequence
   const bool sync = score_sync_plan(a, a.n_heads, nq_max, row_dim, B, cols, groups, sync_region, logits_bytes, P.sc);
-  if (sync && P.sc.tw == 8) {
+  if (sync && B * cols >= kScoreSyncPositions) {
     P.form = ScorePrep::kSync;
     return;
   }
   ChunkCall& cc = P.cc;
-  if (score_chunk_call(a, a.n_heads, nq_max, row_dim, B, groups, cc)) {
+  if (B <= kScoreSyncMaxBatch && score_chunk_call(a, a.n_heads, nq_max, row_dim, B, groups, cc)) {
     cc.sync = sync_region;
-    const int64_t units = (int64_t)B * (a.per_layer ? a.n_layers : 1), chunks8 = (cols + 511) / 512;
+    const int64_t chunks8 = (cols + 511) / 512;
     const int tiles = cc.nt == 0 ? 1 : cc.nu * cc.nt;
     int64_t most;  // chunks of 512 positions, all sequences
-    if (a.per_layer || (a.n_layers == 1 && cc.nt > 0)) most = 16;
-    else if (a.n_layers == 1) most = kScoreSyncCUs;
-    else most = cc.nt == 0 ? 2 * kScoreSyncCUs : 4 * kScoreSyncCUs;
+    if (L == 1) most = cc.nt == 0 ? kScoreSyncCUs : 16;
+    else if (cc.nt == 0) most = a.n_heads * nq_max <= 4 ? kScoreSyncCUs : 2 * kScoreSyncCUs;
+    else most = 4 * kScoreSyncCUs;
     cc.tw = B * chunks8 <= 64 || most == 16 ? 4 : 8;
     const int64_t chunks = (cols + 64 * cc.tw - 1) / (64 * cc.tw);
-    const int once_cols = 16 * tiles * (a.per_layer ? 1 : a.n_layers);
-    if (score_once_supported(cc) && B * chunks8 <= most && chunks <= kChunkMaxOnce && units <= kScoreSyncMaxBatch &&
-        units * chunks <= INT32_MAX / 2 && (size_t)units * (chunks + 1) * once_cols * 2 * sizeof(float) <= logits_bytes) {
+    if (score_once_supported(cc) && B * chunks8 <= most && chunks <= (L == 1 ? kChunkMaxOnce / 2 : kChunkMaxOnce) &&
+        (size_t)(chunks + 1) * 16 * tiles * 2 * sizeof(float) <= logits_bytes) {
       cc.chunks = (int32_t)chunks;
       cc.share_merge = B * chunks <= 2 * kScoreSyncCUs ? 1 : 0;
       P.form = ScorePrep::kOnce;
@@ -599,15 +619,16 @@ void score_choose(ScorePrep& P, int row_dim, int B, int32_t nq_max, int64_t cols
     // chunks of 1024 positions, or of 512 where those would leave a CU less than two
     cc.tw = B * chunks8 <= 2 * kScoreSyncCUs ? 8 : 16;
     const int64_t rchunks = (cols + 64 * cc.tw - 1) / (64 * cc.tw);
-    if (score_reread_supported(cc) && B * chunks8 >= kScoreSyncCUs && (int64_t)B * a.n_layers <= kScoreSyncMaxBatch &&
-        (size_t)B * a.n_layers * (rchunks + 1) * 16 * tiles * 2 * sizeof(float) <= logits_bytes &&
-        2 * units * rchunks * (a.n_layers + 1) <= INT32_MAX) {
+    const int64_t least = a.n_heads * nq_max >= 48 ? kScoreSyncCUs : 2 * kScoreSyncCUs;
+    if (score_reread_supported(cc) && B * chunks8 >= least && (int64_t)B * L <= kScoreSyncMaxBatch &&
+        (size_t)(rchunks + 1) * 16 * tiles * 2 * sizeof(float) <= logits_bytes &&
+        2 * (int64_t)B * rchunks * (L + 1) <= kChunkMaxBlocks) {
       cc.chunks = (int32_t)rchunks;
       P.form = ScorePrep::kReread;
       return;
     }
   }
-  if (sync) P.form = ScorePrep::kSync;
+  if (sync && L > 1) P.form = ScorePrep::kSync;
 }
 
 // The launch arguments of one or two calls of score_once.hip, or of one of score_reread.hip.
@@ -660,31 +681,44 @@ dustin_status score_fill(ScorePrep& P, int row_dim, int B, int32_t nq_max, int64
   a.stats = reinterpret_cast<float*>(base + kScoreSyncBytes + logits_bytes);
   P.row_dim = row_dim;
   P.B = B;
-  score_choose(P, row_dim, B, nq_max, cols, groups, reinterpret_cast<int32_t*>(base), logits_bytes);
+  score_choose(P, row_dim, B, nq_max, cols, groups, reinterpret_cast<int32_t*>(base));
   return DUSTIN_OK;
 }
 
+// Launches a prepared call: with per-layer outputs, one layer a launch (score_sync.hip) or as many
+// as the workspace's counters and a grid hold, one after the other.
 dustin_status score_run(const ScorePrep& P, void* stream) {
   if (P.empty) return DUSTIN_OK;
-  hipError_t e;
-  switch (P.form) {
-    case ScorePrep::kSync: {
+  const ScoreArgs& a = P.a;
+  hipStream_t const st = static_cast<hipStream_t>(stream);
+  if (P.form == ScorePrep::kTwoPass)
+    return launch_score(a, P.B, P.n_groups, P.max_group, P.row_dim, st) == hipSuccess ? DUSTIN_OK : DUSTIN_ERR_LAUNCH;
+  int most = a.n_layers;
+  if (a.per_layer) {
+    int64_t n = 1;
+    if (P.form != ScorePrep::kSync) {
+      n = kScoreSyncMaxBatch / P.B;
+      const int64_t blocks = 4 * (int64_t)P.B * P.cc.chunks;
+      if (n > kChunkMaxBlocks / blocks) n = kChunkMaxBlocks / blocks;
+    }
+    if (n < most) most = (int)n;
+  }
+  for (int l0 = 0; l0 < a.n_layers; l0 += most) {
+    const int n = a.n_layers - l0 < most ? a.n_layers - l0 : most;
+    hipError_t e;
+    if (P.form == ScorePrep::kSync) {
       SyncArgs sa;
       memset(&sa, 0, sizeof sa);
-      sa.call[0] = P.sc;
-      e = launch_score_sync(sa, static_cast<hipStream_t>(stream));
-      break;
+      sa.call[0] = score_layers_of(P.sc, l0, n, a.out_sl);
+      e = launch_score_sync(sa, st);
+    } else {
+      const ChunkCall c = score_layers_of(P.cc, l0, n, a.out_sl);
+      const ChunkArgs ca = score_chunk_args(&c, nullptr, P.form == ScorePrep::kReread);
+      e = P.form == ScorePrep::kOnce ? launch_score_once(ca, 1, st) : launch_score_reread(ca, st);
     }
-    case ScorePrep::kOnce:
-      e = launch_score_once(score_chunk_args(&P.cc, nullptr, false), 1, static_cast<hipStream_t>(stream));
-      break;
-    case ScorePrep::kReread:
-      e = launch_score_reread(score_chunk_args(&P.cc, nullptr, true), static_cast<hipStream_t>(stream));
-      break;
-    default:
-      e = launch_score(P.a, P.B, P.n_groups, P.max_group, P.row_dim, static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return DUSTIN_ERR_LAUNCH;
   }
-  return e == hipSuccess ? DUSTIN_OK : DUSTIN_ERR_LAUNCH;
+  return DUSTIN_OK;
 }
 
 // Validates Eq. 5 for n_layers layers that share shapes, summed into one output (or each

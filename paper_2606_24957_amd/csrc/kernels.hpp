@@ -70,6 +70,7 @@ constexpr int kScoreMaxPairs = 1024;     // (layer, head, query) rows one output
 constexpr int kSyncWaves = 16;             // waves per single-pass workgroup
 constexpr int kScoreSyncMaxBatch = 2048;   // sequences the counters cover
 constexpr int kScoreSyncMaxChunks = 128;   // chunks of one sequence (far below the chip's CUs)
+constexpr int64_t kScoreSyncPositions = INT64_C(192) * 2048;  // positions from which chunks of 2048 fill the chip
 constexpr int kScoreSyncCUs = 256;         // MI355X compute units: one single-pass workgroup each
 constexpr size_t kScoreSyncBytes = 16896;  // 2 * kScoreSyncMaxBatch counters + the flag, 256-aligned
 static_assert(kScoreSyncBytes >= (2 * kScoreSyncMaxBatch + 1) * 4 && kScoreSyncBytes % 256 == 0, "sync region");
@@ -157,6 +158,7 @@ hipError_t launch_score_sync_pair(const SyncArgs& a, hipStream_t stream);
 // ---- score calls by chunks of four-wave workgroups (score_once.hip, score_reread.hip) ----
 constexpr int kChunkWaves = 4;
 constexpr int kChunkMaxTW = 16;            // most 16-position tiles per wave
+constexpr int64_t kChunkMaxBlocks = (INT64_C(1) << 32) / (kChunkWaves * kWave) - 1;  // a grid has less than 2^32 threads
 constexpr int kChunkMaxOnce = 256;         // most chunks of a sequence in score_once.hip
 // Most int32 between the counters of two units: as far apart as the region allows, so that the
 // polls and counts of one unit's workgroups do not queue behind another's in a cache line and memory

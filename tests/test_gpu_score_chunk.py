@@ -134,6 +134,34 @@ def test_k_read_twice(lens, n_layers, per_layer, page_size):
 
 
 @pytest.mark.parametrize("model,n_layers,nq_max,lens", [
+    # small calls in one pass, up to and past their last chunk, in two passes and in 16-wave workgroups
+    (TARGET, 3, 1, [9000, 1, 0, 4100]), (TARGET, 3, 1, [32768, 32767, 0, 5]), (TARGET, 3, 1, [32800, 40, 0, 5]),
+    (DRAFT, 3, 4, [65536]), (DRAFT, 2, 4, [65537]), (DRAFT, 2, 4, [24700] * 15 + [3]), (DRAFT, 3, 5, [2048] * 4),
+    (DRAFT, 3, 5, [2049] * 4), (ALL, 3, 4, [8192]), (ALL, 3, 4, [8193]),
+    # K read twice from 512-position chunks on every CU on (fewer than 48 pairs: two), and not before
+    (ALL, 3, 4, [32768] * 3 + [32700]), (ALL, 3, 4, [32256] * 4), (ALL, 3, 3, [32768] * 8), (ALL, 3, 3, [32768] * 4),
+    # more (layer, sequence) units than there are counters: several launches
+    (ALL, 24, 4, [1536] * 85 + [700]), (DRAFT, 32, 4, [257] * 65 + [0]),
+])
+def test_a_layer_has_the_bits_of_a_call_of_its_own(model, n_layers, nq_max, lens):
+    B, N = len(lens), max(lens)
+    nq = [max(1, nq_max - b % 3) if b else nq_max for b in range(B)]
+    qs, ks, _, _, seq, nqt = _inputs(model, lens, nq, n_layers, 700 + N)
+    out = torch.full((n_layers, B, 1, N), -5.0, device=DEV)
+    for _ in range(2):
+        D.score_per_layer(qs, ks, seq, model[3], n_query=nqt, out=out, max_len=N)
+    torch.cuda.synchronize()
+    _sync_region_clear()
+    for l in range(n_layers):
+        one = torch.full((B, 1, N), -5.0, device=DEV)
+        D.score(qs[l], ks[l], seq, model[3], n_query=nqt, out=one, max_len=N)
+        assert torch.equal(one, out[l]), f"layer {l}"
+    sums = (out.double() * (out >= 0)).sum(dim=(2, 3)).cpu()
+    want = torch.tensor([len(model[3]) * t if n else 0 for n, t in zip(lens, nq)], dtype=torch.float64)
+    assert torch.allclose(sums, want.expand(n_layers, B), rtol=1e-4, atol=0)
+
+
+@pytest.mark.parametrize("model,n_layers,nq_max,lens", [
     (TARGET, 1, 4, SMALL), (DRAFT, 3, 4, SMALL), (DRAFT, 3, 5, LARGE), (ALL, 1, 3, SMALL),
     (ALL, 1, 4, [65700, 1, 1023]), (ALL, 3, 3, [65700, 300, 1023]),
 ])
