@@ -601,6 +601,7 @@ void score_choose(ScorePrep& P, int row_dim, int B, int32_t nq_max, int64_t cols
   ChunkCall& cc = P.cc;
   if (B <= kScoreSyncMaxBatch && score_chunk_call(a, a.n_heads, nq_max, row_dim, B, groups, cc)) {
     cc.sync = sync_region;
+    cc.polls = env_int("DUSTIN_SCORE_POLLS", kChunkPolls);
     const int64_t chunks8 = (cols + 511) / 512;
     const int tiles = cc.nt == 0 ? 1 : cc.nu * cc.nt;
     int64_t most;  // chunks of 512 positions, all sequences

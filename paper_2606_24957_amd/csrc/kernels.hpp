@@ -165,6 +165,10 @@ constexpr int kChunkMaxOnce = 256;         // most chunks of a sequence in score
 // channel (per-layer calls of 16 units of 8192 positions, 28 pairs: adjacent 26.3 us, apart 14.7;
 // score_reread.hip, 24 layers of 16 x 16384, 56 pairs: 866 us, 624).
 constexpr int kChunkSyncStride = 64;
+// Looks at a counter (each a memory round trip) before a wait ends: some milliseconds, where calls that
+// share the chip with nobody need up to 512 (24 pairs, three layers of 16 x up to 32768, several rounds
+// of workgroups: 77 us, with 128 looks 1041).
+constexpr int kChunkPolls = 1 << 12;
 constexpr int kChunkMaxTiles = 4;          // most column tiles of 16 pairs
 constexpr int kChunkMaxQ = 12;             // most column tiles times layers that one output sums (score_reread.hip)
 
@@ -183,7 +187,8 @@ struct ChunkCall {
   float* out;
   int64_t out_sb, out_sl;
   float* stats;   // (max, sum of exp2) of every chunk and column
-  int32_t* sync;  // the workspace's counter region (zero between calls) and timeout flag
+  int32_t* sync;  // the workspace's counter region (zero between calls)
+  int32_t polls;  // looks at a counter after which a workgroup waits for the others no longer
   float scale_log2;
   int32_t batch, n_layers, per_layer, head_dim, nu, nt, tw, chunks;
   int32_t sync_stride;  // the launcher's: int32 between two units' counters

@@ -22,7 +22,6 @@ namespace dustin {
 namespace {
 
 constexpr int kChunkThreads = kChunkWaves * kWave;
-constexpr int kSpinLimit = 1 << 16;  // polls of a counter (each a memory round trip)
 constexpr int kChunkMaxCols = 96;     // columns of one publish: layers held at once times column tiles times 16
 constexpr int kChunkMergeLoads = 8;   // summaries a thread loads at once when it merges
 
@@ -64,6 +63,7 @@ struct ChunkLds {
   float2 st[kChunkWaves][kChunkMaxCols];
   float2 part[kChunkThreads];
   float2 mz[kChunkMaxQ * 16];
+  int go[2];  // the waits' outcomes, for the workgroup
   union {
     u32x4 q[kChunkMaxQ * 2 * kWave];
     uint32_t hist[kDigitBins];
@@ -108,15 +108,24 @@ struct ScoreChunk {
 
   __device__ __forceinline__ ScoreChunk(const ChunkCall& a_, int layer0_, int b_, int c_, ChunkLds& lds_)
       : a(a_), lds(lds_), c(c_), b(b_), layer0(layer0_) {
-    lane = threadIdx.x & (kWave - 1);
-    wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    place();
+    N = a.dims.len(b);
+  }
+
+  // This thread's place, opaque to the compiler: a second pass over chunks (after a wait that ran
+  // out) would otherwise share what the first one computed from it, in registers held all the while.
+  __device__ __forceinline__ void place() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    lane = t & (kWave - 1);
+    wave = __builtin_amdgcn_readfirstlane(t / kWave);
     lr = lane & 15;
     lg = lane >> 4;
-    N = a.dims.len(b);
   }
 
   // Row offsets, the first load stages, columns and queries.
   __device__ __forceinline__ void begin() {
+    place();
     rows(TW);
 #pragma unroll
     for (int qi = 0; qi < NB - 1; ++qi) issue(rsrc(layer0 + qi / NST), qi % NST / SPT, qi % SPT, buf[qi]);
@@ -294,8 +303,8 @@ struct ScoreChunk {
   }
   // All threads: the G chunks' summaries of a unit ([chunk][NC] at `stats`), slice sl merging
   // chunks sl, sl + kSlices, ... in order, then the slices in order: columns' (M, 1 / Z) into
-  // lds.mz.
-  __device__ __forceinline__ void merge_chunks(const float2* stats, int G) const {
+  // mz (LDS).
+  __device__ __forceinline__ void merge_chunks(const float2* stats, int G, float2* mz) const {
     constexpr int kCols = NC <= 16 ? 16 : (NC <= 32 ? 32 : (NC <= 64 ? 64 : 128));
     constexpr int kSlices = kChunkThreads / kCols;
     const int col = threadIdx.x % kCols, sl = threadIdx.x / kCols;
@@ -320,7 +329,7 @@ struct ScoreChunk {
         const float2 v = lds.part[i * kCols + threadIdx.x];
         merge_ms(M, Z, v.x, v.y);
       }
-      lds.mz[threadIdx.x] = normaliser(M, Z);
+      mz[threadIdx.x] = normaliser(M, Z);
     }
     __syncthreads();
   }
@@ -374,16 +383,14 @@ __device__ __forceinline__ void clear_hist(ChunkLds& lds) {
   for (int i = threadIdx.x; i < kDigitBins; i += kChunkThreads) lds.hist[i] = 0u;
 }
 
-// One lane waits (bounded) until *word >> shift reaches `target`; on a timeout it sets `flag`.
+// One lane waits until *word >> shift reaches `target`, for at most `polls` more looks at it.
 template <int kSleep>
-__device__ __forceinline__ void wait_count(const int* word, int shift, int target, int* flag) {
-  for (int spins = 0; __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> shift < target;) {
+__device__ __forceinline__ bool wait_count(const int* word, int shift, int target, int polls) {
+  for (; __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> shift < target; --polls) {
+    if (polls <= 0) return false;
     __builtin_amdgcn_s_sleep(kSleep);
-    if (++spins > kSpinLimit) {
-      __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      break;
-    }
   }
+  return true;
 }
 
 }  // namespace

@@ -15,13 +15,12 @@
 // once per layer, in two launches, took 22 + 36 us for a step of 4 x 8192 positions over two
 // target and three draft KV heads' layers, now 19 in one; one sequence of 32768 took 49, now 21.
 //
-// Waiting is safe without a cooperative launch.  Workgroups are dispatched in id order on each
-// XCD, and a unit's chunks have consecutive ids, so the chunks of the first unfinished unit hold
-// slots or are next in line for those that earlier units free.  A unit's chunks (at most 256,
-// 32 on an XCD) take at most half of the 64 or more workgroups that an XCD's 32 CUs hold, so
-// launches on two streams cannot starve each other's first units either.  The wait is bounded
-// all the same: on a timeout the workgroup sets a flag in the workspace and goes on.  The last
-// chunk of a unit to leave returns the unit's counters to zero.
+// A wait ends without a cooperative launch: workgroups are dispatched in id order on each XCD, and a
+// unit's chunks have consecutive ids, so that they hold slots or are next in line.  But workgroups of
+// launches on other streams may hold those slots while they wait for this one's, some on one XCD
+// and some on another.  So a workgroup waits for a bounded time only, and then depends on nobody:
+// it forms every chunk's statistics itself, stores them where their owners do (the same bits), and
+// goes on.  The last chunk of a unit to leave returns the unit's counters to zero.
 #include "score_chunk.hpp"
 
 namespace dustin {
@@ -35,52 +34,60 @@ namespace {
 // 127 us, shared 153), and the host leaves share_merge unset.
 constexpr int kMergeAll = 4 * kChunkThreads * kChunkMergeLoads;
 
+// Column col's (M, 1 / Z) over the unit's G chunks, by one wave (lane 0 holds it).
+template <class S>
+__device__ __forceinline__ float2 merge_column(const ScoreChunk<S>& k, const float2* stats, int G, int col) {
+  float M = -INFINITY, Z = 0.f;
+  float2 v[kChunkMaxOnce / kWave];
+#pragma unroll
+  for (int i = 0; i < kChunkMaxOnce / kWave; ++i)
+    v[i] = load_pair_sc1(stats + min(k.lane + i * kWave, G - 1) * S::NC + col);
+#pragma unroll
+  for (int i = 0; i < kChunkMaxOnce / kWave; ++i)
+    if (k.lane + i * kWave < G) merge_ms(M, Z, v[i].x, v[i].y);
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const float mo = __shfl_xor(M, off), so = __shfl_xor(Z, off);
+    merge_ms(M, Z, mo, so);
+  }
+  return k.normaliser(M, Z);
+}
+
 // The unit's workgroups share the merge of its G chunks' summaries: wave w of chunk c merges column
 // c + w G and publishes its (M, 1 / Z) behind the summaries, counted in the high half of *done;
-// every workgroup then reads all of them into lds.mz.
+// every workgroup then reads all of them into lds.mz, or, should they not come, merges them all.
 template <class S>
 __device__ __forceinline__ void merge_shared(const ScoreChunk<S>& k, float2* stats, int G, int* done) {
   constexpr int NC = S::NC;
   const int col = k.c + k.wave * G;
   if (col < NC) {  // uniform over the wave
-    float M = -INFINITY, Z = 0.f;
-    float2 v[kChunkMaxOnce / kWave];
-#pragma unroll
-    for (int i = 0; i < kChunkMaxOnce / kWave; ++i)
-      v[i] = load_pair_sc1(stats + min(k.lane + i * kWave, G - 1) * NC + col);
-#pragma unroll
-    for (int i = 0; i < kChunkMaxOnce / kWave; ++i)
-      if (k.lane + i * kWave < G) merge_ms(M, Z, v[i].x, v[i].y);
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-      const float mo = __shfl_xor(M, off), so = __shfl_xor(Z, off);
-      merge_ms(M, Z, mo, so);
-    }
-    if (k.lane == 0) {
-      const float2 n = k.normaliser(M, Z);
-      store_pair_sc1(stats + k.a.chunks * NC + col, n.x, n.y);
-    }
+    const float2 n = merge_column(k, stats, G, col);
+    if (k.lane == 0) store_pair_sc1(stats + k.a.chunks * NC + col, n.x, n.y);
     k.stores_done();
     if (k.lane == 0) __hip_atomic_fetch_add(done, 0x10000, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (threadIdx.x == 0) wait_count<1>(done, 16, NC, k.a.sync + 2 * kScoreSyncMaxBatch);
+  if (threadIdx.x == 0) k.lds.go[1] = wait_count<1>(done, 16, NC, k.a.polls);
   asm volatile("" ::: "memory");  // the columns are read only after the count is complete
   __syncthreads();
-  if ((int)threadIdx.x < NC) k.lds.mz[threadIdx.x] = load_pair_sc1(stats + k.a.chunks * NC + threadIdx.x);
+  if (k.lds.go[1]) {
+    if ((int)threadIdx.x < NC) k.lds.mz[threadIdx.x] = load_pair_sc1(stats + k.a.chunks * NC + threadIdx.x);
+  } else {
+    k.stores_done();  // this wave's count, before the workgroup's departure
+    for (int t = k.wave; t < NC; t += kChunkWaves) {
+      const float2 n = merge_column(k, stats, G, t);
+      if (k.lane == 0) k.lds.mz[t] = n;
+    }
+  }
   __syncthreads();
 }
 
-template <class S>
-__device__ __forceinline__ void score_once(const ChunkCall& a, int unit, int c, ChunkLds& lds) {
-  constexpr int NC = S::NC, LB = S::LB, CT = S::CT, GS = S::GS, TW = S::TW;
-  const int layer0 = a.per_layer ? unit / a.batch : 0;
-  ScoreChunk<S> k(a, layer0, a.per_layer ? unit - layer0 * a.batch : unit, c, lds);
-  const int G = (k.N + S::C - 1) / S::C;  // chunks of this sequence
-  if (c >= G) return;  // uniform over the workgroup
-  if (a.hist) clear_hist(lds);  // the barriers below order this before the counting
+// A wave's (max, sum of exp2) of every column over its chunk, into LDS.  With kKeep, also
+// x = exp2(logit - the group's max) and that max (log2 domain, scaled).
+template <bool kKeep, class S>
+__device__ __forceinline__ void chunk_logits(ScoreChunk<S>& k, f32x4 (&x)[S::LB][S::TW][S::CT],
+                                             float (&gm)[S::LB][S::TW / S::GS][S::CT]) {
+  constexpr int LB = S::LB, CT = S::CT, GS = S::GS;
   k.begin();
-  f32x4 x[LB][TW][CT];        // exp2(logit - the group's max)
-  float gm[LB][TW / GS][CT];  // the group's max (log2 domain, scaled)
   float m[LB][CT], ssum[LB][CT];
 #pragma unroll
   for (int lb = 0; lb < LB; ++lb)
@@ -89,7 +96,7 @@ __device__ __forceinline__ void score_once(const ChunkCall& a, int unit, int c, 
       m[lb][ct] = -INFINITY;
       ssum[lb][ct] = 0.f;
     }
-  k.stream(layer0, [&](int lb, int t0, f32x4 (&xg)[GS][CT]) {
+  k.stream(k.layer0, [&](int lb, int t0, f32x4 (&xg)[GS][CT]) {
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
       const float mg = k.group_max(t0, ct, xg);
@@ -99,19 +106,48 @@ __device__ __forceinline__ void score_once(const ChunkCall& a, int unit, int c, 
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float w = k.weight(xg[i][ct][e], mg);
-          x[lb][t0 + i][ct][e] = w;
+          if (kKeep) x[lb][t0 + i][ct][e] = w;
           add += w;
         }
-      gm[lb][t0 / GS][ct] = mg;
+      if (kKeep) gm[lb][t0 / GS][ct] = mg;
       merge_ms(m[lb][ct], ssum[lb][ct], mg, add);
     }
   });
   k.summarise(m, ssum);
-  __syncthreads();
+}
+
+// Chunk c of a unit.  False when the wait for the others ran out: then kAlone does it, and waits
+// for nobody.
+template <class S, bool kAlone>
+__device__ __forceinline__ bool score_once_chunk(const ChunkCall& a, int unit, int c, ChunkLds& lds) {
+  constexpr int NC = S::NC, LB = S::LB, CT = S::CT, GS = S::GS, TW = S::TW;
+  const int layer0 = a.per_layer ? unit / a.batch : 0;
+  ScoreChunk<S> k(a, layer0, a.per_layer ? unit - layer0 * a.batch : unit, c, lds);
+  const int G = (k.N + S::C - 1) / S::C;  // chunks of this sequence
+  if (c >= G) return true;  // uniform over the workgroup
+  if (a.hist) clear_hist(lds);  // the barriers below order this before the counting
   int* const cnt = a.sync + unit * a.sync_stride;
   int* const done = a.sync + kScoreSyncMaxBatch + unit * a.sync_stride;
   float2* const stats = reinterpret_cast<float2*>(a.stats) + (int64_t)unit * (a.chunks + 1) * NC;
-  if (k.wave == 0) {  // publishes and waits
+  f32x4 x[LB][TW][CT];
+  float gm[LB][TW / GS][CT];
+  if (kAlone)
+    for (k.c = 0; k.c < G; ++k.c) {
+      chunk_logits<false>(k, x, gm);
+      __syncthreads();
+      if (k.wave == 0) {
+        for (int col = k.lane; col < NC; col += kWave) {
+          const float2 v = k.workgroup_summary(col);
+          store_pair_sc1(stats + k.c * NC + col, v.x, v.y);
+        }
+        k.stores_done();
+      }
+      __syncthreads();  // the summary is stored, and the waves' have been read
+    }
+  k.c = c;
+  chunk_logits<true>(k, x, gm);
+  __syncthreads();
+  if (!kAlone && k.wave == 0) {  // publishes and waits
     for (int col = k.lane; col < NC; col += kWave) {
       const float2 v = k.workgroup_summary(col);
       if (G == 1) lds.mz[col] = k.normaliser(v.x, v.y);
@@ -121,15 +157,16 @@ __device__ __forceinline__ void score_once(const ChunkCall& a, int unit, int c, 
       k.stores_done();
       if (k.lane == 0) {
         __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        wait_count<1>(cnt, 0, G, a.sync + 2 * kScoreSyncMaxBatch);
+        lds.go[0] = wait_count<1>(cnt, 0, G, a.polls);
       }
       asm volatile("" ::: "memory");  // the summaries are read only after the count is complete
     }
   }
   __syncthreads();
   if (G > 1) {
+    if (!kAlone && !lds.go[0]) return false;
     constexpr int kCols = NC <= 16 ? 16 : (NC <= 32 ? 32 : (NC <= 64 ? 64 : 128));
-    if (G * kCols <= kMergeAll || !a.share_merge) k.merge_chunks(stats, G);
+    if (G * kCols <= kMergeAll || !a.share_merge) k.merge_chunks(stats, G, lds.mz);
     else merge_shared(k, stats, G, done);
     // the last chunk of the unit to leave returns its counters to zero
     if (threadIdx.x == 0 && (__hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xffff) == G - 1) {
@@ -170,6 +207,14 @@ __device__ __forceinline__ void score_once(const ChunkCall& a, int unit, int c, 
   }
   k.write(acc, layer0, 0, TW);
   k.flush_hist();
+  return true;
+}
+
+template <class S>
+__device__ __forceinline__ void score_once(const ChunkCall& a, int unit, int c, ChunkLds& lds) {
+  if (score_once_chunk<S, false>(a, unit, c, lds)) return;
+  asm volatile("" : "+s"(unit), "+s"(c));  // as ScoreChunk::place()
+  (void)score_once_chunk<S, true>(a, unit, c, lds);
 }
 
 // The calls' chunks unit by unit: the first call's chunks of a unit, then the second's.

@@ -13,10 +13,11 @@
 // (3.2 GB of K) take 576 + 600 us, against 1446 + 571 with the logits written and read.
 //
 // The second kind's blocks of a unit (a sequence, or a (layer, sequence)) follow the first kind's of
-// the unit `lag` later, so that they rarely wait.  The first kind waits for nothing, and the
-// lowest unfinished block id can always go on (blocks are dispatched in id order on each XCD), so
-// nothing here depends on how many workgroups are resident.  The wait is bounded all the same:
-// on a timeout the workgroup sets a flag in the workspace and goes on.
+// the unit `lag` later, so that they rarely wait.  The first kind waits for nothing, and on each XCD
+// blocks are dispatched in id order, so that a launch of its own always goes on.  Beside another
+// launch, second kinds of both may hold the slots of some XCD each that the other's first kind needs:
+// a second-kind block waits for a bounded time only, and then forms the statistics of its unit
+// itself, stores them where the first kind does (the same bits), and goes on.
 #include "score_chunk.hpp"
 
 namespace dustin {
@@ -57,13 +58,13 @@ __device__ __forceinline__ void stream_tiles(ScoreChunk<S>& k, __amdgpu_buffer_r
   }
 }
 
+// The (max, sum of exp2) of every column over chunk c of a layer, into the layer's statistics (by wave
+// 0, complete when it goes on).
 template <class S>
-__device__ __forceinline__ void first_kind(const ChunkCall& a, int layer, int b, int c, ChunkLds& lds) {
+__device__ __forceinline__ void store_summary(const ChunkCall& a, int layer, int b, int c, ChunkLds& lds) {
   constexpr int CT = S::CT, GS = S::GS, NC = S::NC;
   static_assert(S::LB == 1 && NC <= kWave, "one lane per column");
   ScoreChunk<S> k(a, layer, b, c, lds);
-  const int C = kChunkWaves * 16 * a.tw, G = (k.N + C - 1) / C;
-  if (c >= G) return;  // uniform over the workgroup
   k.rows(a.tw);
   const auto rs = k.rsrc(layer);
 #pragma unroll
@@ -93,44 +94,73 @@ __device__ __forceinline__ void first_kind(const ChunkCall& a, int layer, int b,
   });
   k.summarise(m, ssum);
   __syncthreads();
-  float2* const stats = layer_stats<S>(a, layer, b);
-  int* const last = reinterpret_cast<int*>(lds.hist);  // (not counted into here)
   if (k.wave == 0) {
     if (k.lane < NC) {
       const float2 v = k.workgroup_summary(k.lane);
-      store_pair_sc1(stats + c * NC + k.lane, v.x, v.y);
+      store_pair_sc1(layer_stats<S>(a, layer, b) + c * NC + k.lane, v.x, v.y);
     }
     k.stores_done();
-    if (k.lane == 0)
-      *last = __hip_atomic_fetch_add(first_count(a, layer, b), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == G - 1;
-  }
-  __syncthreads();
-  if (!*last) return;
-  k.merge_chunks(stats, G);
-  if (k.wave == 0) {
-    if (k.lane < NC) store_pair_sc1(stats + a.chunks * NC + k.lane, lds.mz[k.lane].x, lds.mz[k.lane].y);
-    k.stores_done();
-    if (k.lane == 0) {
-      __hip_atomic_store(first_count(a, layer, b), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_fetch_add(second_count(a, a.per_layer ? layer * a.batch + b : b), 0x10000, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-    }
   }
 }
 
+// Adds to the unit's counter of merged layers (high half) and finished second-kind blocks (low half);
+// whoever completes both returns it to zero.
+__device__ __forceinline__ void count_second(const ChunkCall& a, int unit, int add, int G) {
+  int* const ready = second_count(a, unit);
+  const int all = (a.per_layer ? 1 : a.n_layers) << 16 | G;
+  if (__hip_atomic_fetch_add(ready, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add == all)
+    __hip_atomic_store(ready, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A block of unit (layer0, b): of the first kind, chunk c of layer layer0 + l, or (l < 0) of the second
+// kind, chunk c.
 template <class S, bool kSum>
-__device__ __forceinline__ void second_kind(const ChunkCall& a, int layer0, int b, int c, ChunkLds& lds) {
+__device__ __forceinline__ void score_block(const ChunkCall& a, int layer0, int b, int l, int c, ChunkLds& lds) {
   constexpr int CT = S::CT, GS = S::GS, NC = S::NC, KS = S::KS;
+  const bool first = l >= 0;
   ScoreChunk<S> k(a, layer0, b, c, lds);
   const int C = kChunkWaves * 16 * a.tw, G = (k.N + C - 1) / C;
   if (c >= G) return;  // uniform over the workgroup
   const int L = kSum ? a.n_layers : 1, unit = kSum ? b : layer0 * a.batch + b;
-  int* const ready = second_count(a, unit);
-  k.rows(a.tw);
+  if (!first) {
+    k.rows(a.tw);
 #pragma unroll
-  for (int r = 0; r < 3; ++r) k.issue(k.rsrc(layer0), r, 0, k.buf[r]);
-  if (threadIdx.x == 0) wait_count<16>(ready, 16, L, a.sync + 2 * kScoreSyncMaxBatch);
-  asm volatile("" ::: "memory");  // the columns are read only after the count is complete
+    for (int r = 0; r < 3; ++r) k.issue(k.rsrc(layer0), r, 0, k.buf[r]);
+    if (threadIdx.x == 0) lds.go[0] = wait_count<16>(second_count(a, unit), 16, L, a.polls);
+    asm volatile("" ::: "memory");  // the columns are read only after the count is complete
+    __syncthreads();
+  }
+  if (first || !lds.go[0]) {  // the statistics of one chunk, or of all of the unit's
+    const int l_end = first ? l + 1 : L, c_end = first ? c + 1 : G;
+    for (l = first ? l : 0; l < l_end; ++l) {
+      const int layer = layer0 + l;
+      for (int cc = first ? c : 0; cc < c_end; ++cc) {
+        store_summary<S>(a, layer, b, cc, lds);
+        if (first && threadIdx.x == 0)
+          lds.go[0] = __hip_atomic_fetch_add(first_count(a, layer, b), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == G - 1;
+        __syncthreads();
+      }
+      if (first && !lds.go[0]) return;
+      k.place();
+      float2* const stats = layer_stats<S>(a, layer, b);
+      k.merge_chunks(stats, G, lds.mz + (first ? 0 : l * NC));
+      if (first) {  // the last chunk of its layer
+        if (k.wave == 0) {
+          if (k.lane < NC) store_pair_sc1(stats + a.chunks * NC + k.lane, lds.mz[k.lane].x, lds.mz[k.lane].y);
+          k.stores_done();
+          if (k.lane == 0) {
+            __hip_atomic_store(first_count(a, layer, b), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            count_second(a, unit, 0x10000, G);
+          }
+        }
+        return;
+      }
+    }
+    k.place();
+    k.rows(a.tw);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) k.issue(k.rsrc(layer0), r, 0, k.buf[r]);
+  }
   k.columns();
   u32x4 q[CT][KS];
   if (kSum) {  // every layer's queries as the lanes take them, by wave 0
@@ -148,9 +178,10 @@ __device__ __forceinline__ void second_kind(const ChunkCall& a, int layer0, int 
     k.load_q(layer0, q);
     k.sign_q(q);
   }
-  __syncthreads();
-  for (int i = threadIdx.x; i < L * NC; i += kChunkThreads)
-    lds.mz[i] = load_pair_sc1(layer_stats<S>(a, layer0 + i / NC, b) + a.chunks * NC + i % NC);
+  if (lds.go[0]) {
+    for (int i = threadIdx.x; i < L * NC; i += kChunkThreads)
+      lds.mz[i] = load_pair_sc1(layer_stats<S>(a, layer0 + i / NC, b) + a.chunks * NC + i % NC);
+  }
   __syncthreads();
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};  // lane lr: tile lr's positions 4 lg .. + 3
   for (int l = 0; l < L; ++l) {
@@ -195,10 +226,7 @@ __device__ __forceinline__ void second_kind(const ChunkCall& a, int layer0, int 
   }
   k.write(acc, layer0, 0, a.tw);
   k.flush_hist();
-  // the last chunk of the unit to leave returns its counter to zero
-  if (threadIdx.x == 0 &&
-      (__hip_atomic_fetch_add(ready, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xffff) == G - 1)
-    __hip_atomic_store(ready, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0) count_second(a, unit, 1, G);
 }
 
 // Block order: `lag` units' first kind, then unit after unit the first kind of unit j and the second
@@ -226,12 +254,8 @@ __global__ __launch_bounds__(kChunkThreads, 3) void score_reread_kernel(ChunkArg
     u += args.units - args.lag;
   }
   const int part = u / a.batch, b = u - part * a.batch;  // the unit's layer (per-layer outputs), else 0
-  if (r < firsts) {
-    const int l = r / a.chunks;
-    first_kind<S>(a, part + l, b, r - l * a.chunks, lds);
-  } else {
-    second_kind<S, kSum>(a, part, b, r - firsts, lds);
-  }
+  const int l = r / a.chunks, c = r - l * a.chunks;
+  score_block<S, kSum>(a, part, b, r < firsts ? l : -1, c, lds);
 }
 
 using Shape = ChunkShape<64, 2, 2, 4, 1, 2>;

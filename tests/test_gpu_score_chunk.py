@@ -205,6 +205,60 @@ def test_a_key_that_is_not_finite(model, n_layers, lens):
         assert not out[1, 0, :lens[1]].isnan().any()
 
 
+# many chunks of a sequence: merged by all its workgroups together past 64 chunks of 96 columns or
+# 128 of 48 while the call fits the chip in one round (the first three), else by each
+MANY = [
+    (5, [33000, 32768, 40000, 0, 1]), (8, [131072]), (4, [70000, 65536, 513]), (6, [40000] * 6 + [39000]),
+]
+
+
+@pytest.mark.parametrize("nq_max,lens", MANY)
+def test_many_chunks_of_a_sequence(nq_max, lens):
+    nq = [max(1, nq_max - b) for b in range(len(lens))]
+    qs, ks, _, _, seq, nqt = _inputs(DRAFT, lens, nq, 3, 800 + nq_max)
+    out = torch.full((len(lens), 1, max(lens)), -5.0, device=DEV)
+    for _ in range(2):
+        D.score_layers(qs, ks, seq, DRAFT[3], n_query=nqt, out=out, max_len=max(lens))
+    torch.cuda.synchronize()
+    _sync_region_clear()
+    refs = {b: 0.0 for b in range(len(lens))}
+    for q, k in zip(qs, ks):
+        for b, r in _reference(DRAFT, q, k, lens, nq, scale_of(64), range(len(lens))).items():
+            refs[b] = refs[b] + r
+    _check(out, refs, lens, f"{lens}")
+
+
+@pytest.mark.parametrize("model,n_layers,nq_max,lens,per_layer", [
+    (TARGET, 1, 4, SMALL, False), (TARGET, 1, 1, LARGE, False), (DRAFT, 3, 4, LARGE, False), (DRAFT, 3, 6, SMALL, False),
+    (DRAFT, 3, 8, LARGE, False), (ALL, 1, 4, SMALL, False), (ALL, 3, 4, [700, 2700], True),
+    *[(DRAFT, 3, nq, lens, False) for nq, lens in MANY],
+    (ALL, 1, 4, REREAD[0], False), (ALL, 3, 4, REREAD[1], False), (ALL, 2, 4, REREAD[1], True),
+])
+def test_a_wait_that_runs_out_changes_nothing(model, n_layers, nq_max, lens, per_layer, monkeypatch):
+    """With one look at a counter nearly every workgroup stops waiting for the others and forms their
+    statistics itself: the outputs and digit counts keep their bits and the counters return to zero."""
+    B, N = len(lens), max(lens)
+    nq = [max(0, nq_max - b % 3) if b else nq_max for b in range(B)]
+    qs, ks, _, _, seq, nqt = _inputs(model, lens, nq, n_layers, 900 + nq_max)
+    got = {}
+    for polls in (None, "1", "0"):
+        if polls:
+            monkeypatch.setenv("DUSTIN_SCORE_POLLS", polls)
+        hist = D.digit_hist(B, DEV)
+        if per_layer:
+            out = torch.full((n_layers, B, 1, N), -5.0, device=DEV)
+            D.score_per_layer(qs, ks, seq, model[3], n_query=nqt, out=out, max_len=N)
+        else:
+            out = torch.full((B, 1, N), -5.0, device=DEV)
+            plan = D.plan_score_layers(qs, ks, seq, model[3], n_query=nqt, out=out, max_len=N)
+            D.plan_score_calls([plan], digit_hists=[hist])()
+        torch.cuda.synchronize()
+        _sync_region_clear()
+        got[polls] = (out, hist)
+    for polls in ("1", "0"):
+        assert torch.equal(got[polls][0], got[None][0]) and torch.equal(got[polls][1], got[None][1]), polls
+
+
 def test_a_pair_of_small_calls_has_the_bits_of_the_separate_calls():
     """A step's target and draft calls in one launch, 17 pairs and more, both chunk sizes."""
     for lens in (SMALL, LARGE):
