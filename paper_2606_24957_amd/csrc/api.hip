@@ -102,6 +102,7 @@ int attn_row_tiles(int nq_max, int group_size) {
 // slots; beyond kAttnBalancePairs pairs each pair is one workgroup.
 struct AttnSplits {
   int splits, units, min_steps;
+  bool balance;  // more unit slots than pairs
 };
 
 // As many workgroups as the chip holds in one round (256 CUs, one workgroup of four waves
@@ -113,9 +114,16 @@ struct AttnSplits {
 // 1 of 64 29.8; 1024 in 8 of four 13.5, 4 of eight 15.8.  From sixteen steps on, eight splits of
 // two: 512 tokens 13.2 us, 4 of four 14.2, one 14.2.  Below, one: 256 tokens, one KV head, 10.9, 4 of
 // two 13.9.
+// The slots that the pairs leave over go to the longer pairs of a ragged batch; where pairs of equal
+// length have one split, from 64 steps on (20 sequences of 8 KV heads: one of 2048 tokens and 19 of 256
+// 17.9 us, without 30.8, all of 2048 35.2 and 34.1; of 1024 and 256 17.8 and 20.2, all of 1024 22.9 and
+// 21.9; dense, one of 65536 and 19 of 4096 122 and 821).  Few slots are left over from 192 pairs on: long
+// pairs then have as many again as there are pairs, in two rounds, and the last split merges alone (31
+// sequences, dense, one of 32768 and 30 of 4096: 164 us, 255 with eight slots over; 28: 154, 129 with
+// 32; up to 32768 each: 31, 360 and 487; 28, 328 and 390; sparse, 31 of 4096 tokens: 104 and 102).
 AttnSplits attn_splits(int batch, int num_kv_heads, int64_t tokens_per_pair) {
   const int64_t pairs = (int64_t)batch * num_kv_heads;
-  if (pairs <= 0 || pairs > kAttnBalancePairs) return {1, (int)(pairs > 0 ? pairs : 1), 8};
+  if (pairs <= 0 || pairs > kAttnBalancePairs) return {1, (int)(pairs > 0 ? pairs : 1), 8, false};
   const int64_t steps = (tokens_per_pair + 31) / 32;
   int64_t s, min_steps = 8;
   const int forced = env_int("DUSTIN_ATTN_SPLITS", 0);
@@ -132,9 +140,10 @@ AttnSplits attn_splits(int batch, int num_kv_heads, int64_t tokens_per_pair) {
   if (s > kAttnMaxSplits) s = kAttnMaxSplits;
   if (s > steps) s = steps;
   if (s < 1) s = 1;
-  // pairs that do not divide the CUs leave slots over, for the longer pairs of a ragged batch
-  const bool all = forced <= 0 && s > 1 && s == kAttnBalancePairs / pairs;
-  return {(int)s, (int)(all ? kAttnBalancePairs : pairs * s), (int)min_steps};
+  const bool all = forced <= 0 && s == kAttnBalancePairs / pairs && pairs < kAttnBalancePairs && (s > 1 || steps >= 64);
+  const bool two_rounds = pairs > 192 && steps >= 256;
+  const int units = (int)(!all ? pairs * s : two_rounds ? 2 * pairs : kAttnBalancePairs);
+  return {(int)s, units, (int)min_steps, units > pairs};
 }
 
 // Split workspace: a fixed counter region first (the arrival counters and marks of up to
@@ -149,7 +158,7 @@ struct AttnWs {
 
 AttnWs attn_ws_layout(int rows_pad, const AttnSplits& sp) {
   AttnWs w{0, 0, 0, 0};
-  if (sp.splits <= 1) return w;
+  if (!sp.balance) return w;
   w.counters = kAttnMaxPairs * sizeof(int32_t);
   w.acc = round_up((size_t)sp.units * rows_pad * 128 * sizeof(float), kAlign);
   w.ml = round_up((size_t)sp.units * rows_pad * 2 * sizeof(float), kAlign);
@@ -264,8 +273,8 @@ dustin_status prepare_attention(bool sparse, const void* q, int64_t q_sb, int64_
 // Points the split fields at a workspace of at least call.need_ws bytes and launches.
 dustin_status launch_attention(AttnCall& call, bool sparse, void* ws, void* stream) {
   AttnArgs& a = call.a;
-  if (a.splits > 1) {
-    const AttnWs w = attn_ws_layout(a.rows_pad, AttnSplits{a.splits, a.units, a.min_split_steps});
+  if (a.units > a.pairs) {
+    const AttnWs w = attn_ws_layout(a.rows_pad, AttnSplits{a.splits, a.units, a.min_split_steps, true});
     char* base = static_cast<char*>(ws);
     a.counters = reinterpret_cast<int32_t*>(base);
     a.part_acc = reinterpret_cast<float*>(base + w.counters);

@@ -31,7 +31,7 @@
 //          that arrives last reads the other partials back with agent-scope loads,
 //          merges all of them in split order (deterministic whichever arrives last),
 //          writes the output and returns the counter to zero.  From kAttnMergeAlone + 1 splits
-//          on, every split waits (bounded) for the others and merges a slice.  No cache is flushed.
+//          on, in a launch of one round, every split waits (bounded) for the others and merges a slice.  No cache is flushed.
 //
 // Gathered positions (sparse) and page translations (paged) are resolved into an LDS table
 // of physical rows before the token loop, so the loop does no dependent global loads.
@@ -208,11 +208,11 @@ __global__ __launch_bounds__(kW * kWave) void verify_attn_kernel(AttnArgs a) {
     unit = (xcd * A + 7) / 8 + xslot;
     return unit < ((xcd + 1) * A + 7) / 8;
   };
-  // With one split per pair, unit = pair.  With several, every wave sizes the splits from
+  // With as many slots as pairs, unit = pair.  With more, every wave sizes the splits from
   // the actual per-pair token counts below.  Meanwhile the prologue loads of the uniform guess
   // (every pair `splits` splits of split_steps steps, exact when the lengths are equal) are
   // already in flight; they are issued again only if the guess was wrong.
-  const bool balance = a.splits > 1;  // kernel-uniform
+  const bool balance = U > a.pairs;  // kernel-uniform
   int unit = 0;
   const bool guess_ok = unit_of(a.pairs * a.splits, unit);
   int pair = guess_ok ? unit / a.splits : 0;
@@ -1171,7 +1171,7 @@ __global__ __launch_bounds__(kW * kWave) void verify_attn_kernel(AttnArgs a) {
   if (threadIdx.x == 0)
     sm_last = (__hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xffff) == nsplit - 1;
   __syncthreads();
-  if (nsplit > kAttnMergeAlone) {
+  if (nsplit > kAttnMergeAlone && U <= kAttnBalancePairs) {
     // Many splits share the merge: split i merges the i-th slice of the rows' elements, once all
     // have arrived.  There are as many slices as splits, at most the 32 that the mask holds: the
     // longest pairs of a ragged batch take more splits, and the others of theirs only arrive.  One workgroup reads the others' partials at about
@@ -1179,7 +1179,7 @@ __global__ __launch_bounds__(kW * kWave) void verify_attn_kernel(AttnArgs a) {
     // splits took 18.8 us, in sixteen 23.3, and now 15.2 and 14.7; 8192 tokens, dense, in 32
     // splits 38.1, now 20.5.  (With the counters of all pairs in one or two cache lines the
     // polling of 256 workgroups cost all of that gain.)  The wait needs the pair's splits to be resident together (one
-    // launch is one round of workgroups, at most one per CU), and is bounded: a split that
+    // launch is one round of workgroups, at most one per CU; with more, the last merges alone), and is bounded: a split that
     // gives up marks its slice undone and leaves it to the last to arrive.  It marks first and
     // looks at the count again afterwards, and the last arrives first and looks at the marks
     // afterwards, so one of them sees the other (if both do, both write the same bits).

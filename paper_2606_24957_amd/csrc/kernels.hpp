@@ -27,7 +27,7 @@ struct AttnArgs {
   int32_t split_steps;      // 32-token steps per split when every pair is as long as the longest
   int32_t min_split_steps;  // smallest split the kernel's balancing may choose
   int32_t rows_pad;
-  float* part_acc;          // [units, rows_pad, 128], by unit  (splits > 1 only)
+  float* part_acc;          // [units, rows_pad, 128], by unit  (units > pairs only)
   float* part_ml;           // [units, rows_pad, 2]
   int32_t* counters;        // one per kAttnCounterStride, marks from kAttnMaskOffset on; zero between calls
   int32_t merge_spins;      // polls after which a split leaves its share of the merge to the last
@@ -44,7 +44,7 @@ constexpr int kAttnMergeAlone = 3;
 
 // Pairs the attention kernel's split balancing handles (four per lane of one wave); with
 // more pairs there is one workgroup per pair.
-constexpr int kAttnBalancePairs = 256;
+constexpr int kAttnBalancePairs = 256;  // (and one round of its workgroups)
 
 // int32 between the arrival counters of two pairs (each in a cache line and a memory channel of
 // its own: 256 workgroups poll and count at once), and from a counter to the pair's marks of
