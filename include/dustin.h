@@ -384,9 +384,11 @@ dustin_status dustin_topk(const float* s_draft, int64_t d_sb, int64_t d_sg,
  *   workspace  dustin_attn_workspace(..., sparse = 1) bytes, 256-byte aligned (0 bytes,
  *        i.e. NULL, when the batch has enough (b, KV head) pairs to fill the GPU without
  *        splitting the token list).  Its first 256 KB are a counter region (B * num_kv_heads
- *        <= 65536), the partial results of token splits follow.  Zero-fill the workspace once before its first use: every call leaves the
- *        counter region at zero again, so one buffer can then serve calls of any shape.
- *        Calls sharing a workspace must not overlap.
+ *        <= 65536), the partial results of token splits follow.  Where the splits would be
+ *        smaller than 256 tokens, fewer bytes will do if they hold splits of 256 (the output
+ *        then differs by rounding).  Zero-fill the workspace once before its first use: every
+ *        call leaves the counter region at zero again, so one buffer can then serve calls of
+ *        any shape.  Calls sharing a workspace must not overlap.
  * Rounding: bf16 inputs, fp32 MFMA accumulation, fp32 online softmax, probabilities
  * rounded to bf16 before the value product, bf16 output.
  * --------------------------------------------------------------------------------- */

@@ -121,7 +121,8 @@ struct AttnSplits {
 // pairs then have as many again as there are pairs, in two rounds, and the last split merges alone (31
 // sequences, dense, one of 32768 and 30 of 4096: 164 us, 255 with eight slots over; 28: 154, 129 with
 // 32; up to 32768 each: 31, 360 and 487; 28, 328 and 390; sparse, 31 of 4096 tokens: 104 and 102).
-AttnSplits attn_splits(int batch, int num_kv_heads, int64_t tokens_per_pair) {
+// Not `fine`: splits of eight steps or more throughout, in less scratch.
+AttnSplits attn_splits(int batch, int num_kv_heads, int64_t tokens_per_pair, bool fine = true) {
   const int64_t pairs = (int64_t)batch * num_kv_heads;
   if (pairs <= 0 || pairs > kAttnBalancePairs) return {1, (int)(pairs > 0 ? pairs : 1), 8, false};
   const int64_t steps = (tokens_per_pair + 31) / 32;
@@ -132,7 +133,7 @@ AttnSplits attn_splits(int batch, int num_kv_heads, int64_t tokens_per_pair) {
     min_steps = 1;
   } else {
     s = kAttnBalancePairs / pairs;
-    if (s >= 8 && steps >= 16) min_steps = steps >= 32 ? 4 : 2;
+    if (fine && s >= 8 && steps >= 16) min_steps = steps >= 32 ? 4 : 2;
     int64_t most = steps / min_steps;
     if (min_steps == 2) most = 8;
     if (s > most) s = most;
@@ -173,8 +174,9 @@ size_t attn_ws_bytes(int batch, int num_q_heads, int num_kv_heads, int nq_max, i
 }
 
 // A validated attention call: its kernel arguments (workspace fields still unset), the row
-// tiles and cache kind that pick the kernel, and the workspace it needs.  `empty` marks a
-// valid call with nothing to compute.
+// tiles and cache kind that pick the kernel, and the workspace it takes: the fine splits' if
+// ws_bytes holds it, else that of splits of eight steps.  `empty` marks a valid call with nothing
+// to compute.
 struct AttnCall {
   AttnArgs a;
   int rt;
@@ -186,7 +188,8 @@ dustin_status prepare_attention(bool sparse, const void* q, int64_t q_sb, int64_
                                 int32_t num_q_heads, const dustin_kv* k, const dustin_kv* v,
                                 const dustin_batch* bt, const int32_t* idx, int64_t idx_sb,
                                 int64_t idx_sg, const int32_t* count, int32_t groups, float scale,
-                                void* out, int64_t o_sb, int64_t o_st, int64_t o_sh, AttnCall* call) {
+                                void* out, int64_t o_sb, int64_t o_st, int64_t o_sh, size_t ws_bytes,
+                                AttnCall* call) {
   memset(call, 0, sizeof *call);
   if (!batch_ok(bt) || !q || !out || !k || !v) return DUSTIN_ERR_INVALID_ARG;
   if (!isfinite(scale) || !(scale > 0.f)) return DUSTIN_ERR_INVALID_ARG;
@@ -229,8 +232,6 @@ dustin_status prepare_attention(bool sparse, const void* q, int64_t q_sb, int64_
     return DUSTIN_OK;
   }
   const int64_t tokens = sparse ? (int64_t)bt->k_max : (int64_t)bt->max_len;
-  call->need_ws = attn_ws_bytes(B, num_q_heads, Hkv, bt->nq_max, tokens);
-
   AttnArgs& a = call->a;
   a.q = static_cast<const uint16_t*>(q);
   a.q_sb = q_sb;
@@ -255,7 +256,9 @@ dustin_status prepare_attention(bool sparse, const void* q, int64_t q_sb, int64_
   const int rt = attn_row_tiles(bt->nq_max, gs);
   a.rows_pad = rt * 16;
   const int64_t tokens_max = tokens + bt->nq_max;
-  const AttnSplits sp = attn_splits(B, Hkv, tokens_max);
+  AttnSplits sp = attn_splits(B, Hkv, tokens_max);
+  if (sp.min_steps < 8 && ws_bytes < attn_ws_layout(a.rows_pad, sp).total) sp = attn_splits(B, Hkv, tokens_max, false);
+  call->need_ws = attn_ws_layout(a.rows_pad, sp).total;
   a.splits = sp.splits;
   a.units = sp.units;
   const bool sep = rt <= kAttnSepMaxRT;  // the kernels give the window a step of its own there
@@ -292,7 +295,7 @@ dustin_status run_attention(bool sparse, const void* q, int64_t q_sb, int64_t q_
                             size_t ws_bytes, void* stream) {
   AttnCall call;
   const dustin_status st = prepare_attention(sparse, q, q_sb, q_st, q_sh, num_q_heads, k, v, bt, idx, idx_sb,
-                                             idx_sg, count, groups, scale, out, o_sb, o_st, o_sh, &call);
+                                             idx_sg, count, groups, scale, out, o_sb, o_st, o_sh, ws_bytes, &call);
   if (st != DUSTIN_OK || call.empty) return st;
   if (call.need_ws && (!ws || ws_bytes < call.need_ws || !aligned(ws, kAlign))) return DUSTIN_ERR_WORKSPACE;
   return launch_attention(call, sparse, ws, stream);
@@ -1275,7 +1278,8 @@ extern "C" dustin_status dustin_sparse_verify_attn_noalloc(
     void* stream) {
   AttnCall call;
   dustin_status st = prepare_attention(true, q, q_sb, q_st, q_sh, num_q_heads, k, v, bt, idx, idx_sb, idx_sg,
-                                       count, groups, scale, out, o_sb, o_st, o_sh, &call);
+                                       count, groups, scale, out, o_sb, o_st, o_sh,
+                                       DUSTIN_NOALLOC_SCRATCH_BYTES, &call);
   if (st != DUSTIN_OK || call.empty) return st;
   if (call.need_ws > (size_t)DUSTIN_NOALLOC_SCRATCH_BYTES) return DUSTIN_ERR_SCRATCH_LIMIT;
   void* ws = nullptr;

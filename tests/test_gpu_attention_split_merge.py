@@ -86,3 +86,30 @@ def test_more_splits_than_slices(Hq, Hkv, n, t, spins, monkeypatch):
     rows = O.all_rows(B, t, Hq)
     ref = O.attention(bits(q), bits(k), bits(v), n, scale_of(128), rows)
     check_attention(gpu_rows(out, rows), ref, f"{Hq}/{Hkv} {n}")
+
+
+@pytest.mark.parametrize("B,Hkv,n,units", [(1, 8, 2048, 64), (4, 8, 630, 64), (3, 1, 4000, 45), (2, 4, 512, 16)])
+def test_less_scratch_takes_larger_splits(B, Hkv, n, units):
+    """A workspace for splits of eight steps, as a program may have sized it for a larger batch of the
+    same tokens, still does; a smaller one is refused."""
+    Hq, t = Hkv * 8, 5
+    g = torch.Generator(device=DEV).manual_seed(n)
+    q = torch.randn(B, t, Hq, 128, device=DEV, dtype=torch.bfloat16, generator=g)
+    k, v = (torch.randn(B, n + t, Hkv, 128, device=DEV, dtype=torch.bfloat16, generator=g) for _ in range(2))
+    seq = torch.tensor([n - 3 * b for b in range(B)], dtype=torch.int32, device=DEV)
+    out = torch.full_like(q, float("nan"))
+    call = D.plan_dense_verify_attn(q, k, v, seq, max_len=n, out=out)
+    rows_pad, full = 48, call._args[-2]
+    less = (1 << 18) + units * rows_pad * (128 + 2) * 4
+    assert less < full
+    with_bytes = lambda x: D.Call(call._fn, call._args[:-2] + (x, call._args[-1]), call._what, call._keep, out)
+    with pytest.raises(D.DustinError) as e:
+        with_bytes(less - 1)()
+    assert e.value.status == D.ERR_WORKSPACE
+    for _ in range(2):
+        with_bytes(less)()
+    torch.cuda.synchronize()
+    _counters_clear()
+    rows = O.all_rows(B, [t] * B, Hq)
+    ref = O.attention(bits(q), bits(k), bits(v), seq.tolist(), scale_of(128), rows)
+    check_attention(gpu_rows(out, rows), ref, f"{B} x {Hkv} {n}")
