@@ -100,7 +100,7 @@ def test_less_scratch_takes_larger_splits(B, Hkv, n, units):
     out = torch.full_like(q, float("nan"))
     call = D.plan_dense_verify_attn(q, k, v, seq, max_len=n, out=out)
     rows_pad, full = 48, call._args[-2]
-    less = (1 << 18) + units * rows_pad * (128 + 2) * 4
+    less = (1 << 18) + sum(-(-units * rows_pad * x * 4 // 256) * 256 for x in (128, 2))
     assert less < full
     with_bytes = lambda x: D.Call(call._fn, call._args[:-2] + (x, call._args[-1]), call._what, call._keep, out)
     with pytest.raises(D.DustinError) as e:
