@@ -267,7 +267,7 @@ dustin_status prepare_attention(bool sparse, const void* q, int64_t q_sb, int64_
   const int64_t steps_max = sep ? (tokens > 0 ? (tokens + 31) / 32 : 1) : (tokens_max + 31) / 32;
   a.split_steps = (int)((steps_max + a.splits - 1) / a.splits);
   a.min_split_steps = sp.min_steps;
-  a.merge_spins = env_int("DUSTIN_ATTN_MERGE_SPINS", 1 << 14);
+  a.merge_spins = env_int("DUSTIN_ATTN_MERGE_SPINS", kAttnMergeSpins);
   call->rt = rt;
   call->paged = kv.page_table != nullptr;
   return DUSTIN_OK;

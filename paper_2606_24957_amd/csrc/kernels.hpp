@@ -42,6 +42,13 @@ constexpr int kAttnSepMaxRT = 3;
 // tokens, two splits: 35.1 us, shared 37.5).
 constexpr int kAttnMergeAlone = 3;
 
+// Looks at the arrival counter after which a split waits no longer: about a millisecond, which bounds
+// what splits lose that hold CUs while another launch holds those of the splits they wait for.  Alone,
+// 16 sequences, dense, one of 65536 tokens and 15 of 4096, need the most: 99 us with 256 looks, 116
+// with 64, 130 with one (8 KV heads of 2048 tokens: 14.6 us with 16 looks, 50 with one).  Two streams
+// of such launches in turn take no longer a pair than two launches on one.
+constexpr int kAttnMergeSpins = 1 << 10;
+
 // Pairs the attention kernel's split balancing handles (four per lane of one wave); with
 // more pairs there is one workgroup per pair.
 constexpr int kAttnBalancePairs = 256;  // (and one round of its workgroups)
