@@ -8,8 +8,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdustin.so")
-SOURCES = ["api.hip", "attn.hip", "score.hip", "score_sync.hip", "score_once.hip", "score_reread.hip", "topk.hip", "kv.hip", "page.hip", "arr.hip",
-           "probe.hip"]
+SOURCES = ["score_once_pair.hip", "score_once.hip", "api.hip", "attn.hip", "score.hip", "score_sync.hip",
+           "score_reread.hip", "topk.hip", "kv.hip", "page.hip", "arr.hip", "probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 

@@ -436,7 +436,7 @@ bool score_sync_plan(const ScoreArgs& a, int32_t n_heads, int32_t nq_max, int ro
   return true;
 }
 
-// The call by chunks of four-wave workgroups (score_once.hip, score_reread.hip), for one output
+// The call by chunks of four-wave workgroups (score_once.hpp, score_reread.hip), for one output
 // group, positions as rows and pairs that fit the column tiles of their KV heads (a's heads,
 // layers, cache view, dims and output fields set): fills cc, the workspace, chunk and stats
 // fields aside, and returns true, or false when neither form takes the call.
@@ -584,14 +584,15 @@ struct ScorePrep {
 //   single pass, 16-wave workgroups (score_sync.hip): at most 16 pairs, from 393216 positions of
 //     all sequences on while the chunks of 2048 fit the chip in one round; per-layer outputs one layer
 //     a launch (16 layers of 16 x 32768, draft: 676 us, two passes 678).  Also smaller calls of summed
-//     layers that the next form does not take.
-//   single pass, small calls (score_once.hip): one layer up to one 512-position chunk per CU and 65536
+//     layers of other shapes than a draft's.
+//   single pass, small calls (score_once.hpp): one layer up to one 512-position chunk per CU and 65536
 //     positions of a sequence (target of 4 x 32768: 31 us, two passes 30, a launch less; draft's layer
 //     13 against 23; a sequence of 131072 in 16 per-layer outputs 250 us, two passes 178); a draft's
-//     three layers up to two chunks per CU (8 x 32768: 43 us against 60; with at most four pairs, whose
-//     logits are few, up to one: 5 x 32768 39 us against 34), and with 17 to 32 pairs, whose logits
+//     summed layers up to two chunks per CU (8 x 32768, two layers 33 us against 43, three 43 against 60,
+//     four 53 against 89, five 94 against 108; with at most four pairs, whose logits are few, up to one:
+//     5 x 32768 39 us against 34), and three layers of 17 to 32 pairs, whose logits
 //     make two passes longer, up to four (8 x 65536, 24
-//     pairs: 127 us against 155; past them a ragged batch has several rounds of workgroups
+//     pairs: 116 us against 155; past them a ragged batch has several rounds of workgroups
 //     of sequences that end apart, 177 us against 164 at 16 x up to 62922).  Chunks of 256 positions fill
 //     the chip better up to 32768 positions (target and draft 21 us against 24), those of 512 beyond.
 //     Single layers of more than 16 pairs: up to 8192 positions.
@@ -644,7 +645,7 @@ void score_choose(ScorePrep& P, int row_dim, int B, int32_t nq_max, int64_t cols
   if (sync && L > 1) P.form = ScorePrep::kSync;
 }
 
-// The launch arguments of one or two calls of score_once.hip, or of one of score_reread.hip.
+// The launch arguments of one or two calls of score_once.hpp, or of one of score_reread.hip.
 ChunkArgs score_chunk_args(const ChunkCall* c0, const ChunkCall* c1, bool reread) {
   ChunkArgs ca;
   memset(&ca, 0, sizeof ca);

@@ -162,11 +162,11 @@ hipError_t launch_score_sync(const SyncArgs& a, hipStream_t stream);
 bool score_sync_pair_supported(const SyncCall& c0, const SyncCall& c1);
 hipError_t launch_score_sync_pair(const SyncArgs& a, hipStream_t stream);
 
-// ---- score calls by chunks of four-wave workgroups (score_once.hip, score_reread.hip) ----
+// ---- score calls by chunks of four-wave workgroups (score_once.hpp, score_reread.hip) ----
 constexpr int kChunkWaves = 4;
 constexpr int kChunkMaxTW = 16;            // most 16-position tiles per wave
 constexpr int64_t kChunkMaxBlocks = (INT64_C(1) << 32) / (kChunkWaves * kWave) - 1;  // a grid has less than 2^32 threads
-constexpr int kChunkMaxOnce = 256;         // most chunks of a sequence in score_once.hip
+constexpr int kChunkMaxOnce = 256;         // most chunks of a sequence in score_once.hpp
 // Most int32 between the counters of two units: as far apart as the region allows, so that the
 // polls and counts of one unit's workgroups do not queue behind another's in a cache line and memory
 // channel (per-layer calls of 16 units of 8192 positions, 28 pairs: adjacent 26.3 us, apart 14.7;
@@ -199,7 +199,7 @@ struct ChunkCall {
   float scale_log2;
   int32_t batch, n_layers, per_layer, head_dim, nu, nt, tw, chunks;
   int32_t sync_stride;  // the launcher's: int32 between two units' counters
-  int32_t share_merge;  // score_once.hip: every workgroup of the call gets a slot at once
+  int32_t share_merge;  // score_once.hpp: every workgroup of the call gets a slot at once
   int32_t extent;  // bytes of K rows one buffer resource covers (a sequence, or the page pool)
   int32_t kv[4];
   int32_t cols[kChunkMaxTiles];
@@ -210,11 +210,11 @@ struct ChunkCall {
 
 struct ChunkArgs {
   ChunkCall call[2];
-  int32_t units, lag;  // the launcher's: score_once.hip, score_reread.hip
+  int32_t units, lag;  // the launcher's: score_once.hpp, score_reread.hip
 };
 static_assert(sizeof(ChunkArgs) <= 4096, "kernel arguments stay within 4 KiB");
 
-// small calls in one pass (score_once.hip): one call, or two in one launch
+// small calls in one pass (score_once.hpp): one call, or two in one launch
 bool score_once_supported(const ChunkCall& c);
 bool score_once_pair_supported(const ChunkCall& c0, const ChunkCall& c1);
 hipError_t launch_score_once(const ChunkArgs& a, int n_calls, hipStream_t stream);

@@ -1,4 +1,4 @@
-// score_chunk.hpp -- what score_once.hip and score_reread.hip share: a workgroup of four waves
+// score_chunk.hpp -- what score_once.hpp and score_reread.hip share: a workgroup of four waves
 // streams the K rows of a chunk of positions and forms the logits of Eq. 5's (head, query) pairs.
 //
 // Wave w takes TW tiles of 16 consecutive positions.  A tile's K rows meet the pairs' columns on
@@ -71,10 +71,12 @@ struct ChunkLds {
 };
 
 // Shapes: row length, used KV heads, column tiles per KV head (0: one tile shared by all),
-// tiles per wave, layers held at once, tiles handed on together.
-template <int D_, int NU_, int NT_, int TW_, int LB_ = 1, int GS_ = 4>
+// tiles per wave, layers held at once, tiles handed on together, and (score_once.hpp) whether LB layers
+// follow LB layers.
+template <int D_, int NU_, int NT_, int TW_, int LB_ = 1, int GS_ = 4, bool kLoop_ = false>
 struct ChunkShape {
   static constexpr int D = D_, NU = NU_, NT = NT_, TW = TW_, LB = LB_;
+  static constexpr bool kLoop = kLoop_;
   static constexpr int CT = NT == 0 ? 1 : NU * NT;  // column tiles
   static constexpr int KS = D / 32;                 // MFMA k-steps of one KV head's row
   static constexpr int HPS = 4 / KS;                // KV heads per load stage (64 bytes per lane)
@@ -123,13 +125,19 @@ struct ScoreChunk {
     lg = lane >> 4;
   }
 
-  // Row offsets, the first load stages, columns and queries.
+  // Row offsets, the first load stages of the layers from layer0 on, columns and queries.
   __device__ __forceinline__ void begin() {
     place();
     rows(TW);
+    first_stages();
+    columns();
+    queries();
+  }
+  __device__ __forceinline__ void first_stages() {
 #pragma unroll
     for (int qi = 0; qi < NB - 1; ++qi) issue(rsrc(layer0 + qi / NST), qi % NST / SPT, qi % SPT, buf[qi]);
-    columns();
+  }
+  __device__ __forceinline__ void queries() {
 #pragma unroll
     for (int lb = 0; lb < LB; ++lb) load_q(layer0 + lb, bq[lb]);
   }

@@ -1,5 +1,5 @@
 // score_sync.hip -- Eq. 5 in one pass, for calls whose (head, query) pairs fit one MFMA
-// column tile and whose chunks fill the chip in one round (score_once.hip takes the smaller ones
+// column tile and whose chunks fill the chip in one round (score_once.hpp takes the smaller ones
 // of the common shapes).
 //
 // The two-pass form (score.hip) writes every pair's logits to the workspace and reads them

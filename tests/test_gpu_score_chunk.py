@@ -1,5 +1,5 @@
 """The score's chunk forms against the oracle at the edges of their rules: small calls in one
-pass (score_once.hip) with chunks of 256 and of 512 positions, one layer and a draft's three, one
+pass (score_once.hpp) with chunks of 256 and of 512 positions, one layer and a draft's three, one
 shared column tile and one per KV head; and K read twice (score_reread.hip) with chunks of 512
 and of 1024 positions, summed, per layer and counted by top key digit.  Lengths sit on, before
 and after chunk and tile edges, with empty sequences, per-sequence query counts (none among
@@ -58,6 +58,9 @@ LARGE = [11300, 512, 513, 511, 7, 0, 1025, 10000, 4097]  # 9 x 23 chunks of 512
     (DRAFT, 3, 4, SMALL, 0), (DRAFT, 3, 4, LARGE, 0), (DRAFT, 3, 3, SMALL, 4),
     (DRAFT, 3, 5, SMALL, 0), (DRAFT, 3, 6, LARGE, 16), (DRAFT, 3, 8, LARGE, 0),
     (DRAFT, 1, 8, SMALL, 0), (ALL, 1, 4, SMALL, 0), (ALL, 1, 3, SMALL, 64),
+    # two and four layers at once, then two after two and one after one
+    (DRAFT, 2, 4, SMALL, 0), (DRAFT, 4, 4, LARGE, 16), (DRAFT, 6, 2, SMALL, 0), (DRAFT, 8, 4, LARGE, 0),
+    (DRAFT, 5, 4, LARGE, 16), (DRAFT, 7, 3, SMALL, 0),
 ])
 def test_small_calls_in_one_pass(model, n_layers, nq_max, lens, page_size):
     nq = [max(0, nq_max - b % 3) if b else nq_max for b in range(len(lens))]
@@ -231,6 +234,8 @@ def test_many_chunks_of_a_sequence(nq_max, lens):
 @pytest.mark.parametrize("model,n_layers,nq_max,lens,per_layer", [
     (TARGET, 1, 4, SMALL, False), (TARGET, 1, 1, LARGE, False), (DRAFT, 3, 4, LARGE, False), (DRAFT, 3, 6, SMALL, False),
     (DRAFT, 3, 8, LARGE, False), (ALL, 1, 4, SMALL, False), (ALL, 3, 4, [700, 2700], True),
+    (DRAFT, 2, 4, LARGE, False), (DRAFT, 4, 4, [70000, 65536, 513], False), (DRAFT, 6, 4, SMALL, False),
+    (DRAFT, 5, 4, LARGE, False),
     *[(DRAFT, 3, nq, lens, False) for nq, lens in MANY],
     (ALL, 1, 4, REREAD[0], False), (ALL, 3, 4, REREAD[1], False), (ALL, 2, 4, REREAD[1], True),
 ])
@@ -259,13 +264,15 @@ def test_a_wait_that_runs_out_changes_nothing(model, n_layers, nq_max, lens, per
         assert torch.equal(got[polls][0], got[None][0]) and torch.equal(got[polls][1], got[None][1]), polls
 
 
-def test_a_pair_of_small_calls_has_the_bits_of_the_separate_calls():
-    """A step's target and draft calls in one launch, 17 pairs and more, both chunk sizes."""
+@pytest.mark.parametrize("n_layers,gamma", [(1, 4), (2, 4), (3, 3), (3, 6), (4, 4), (5, 2), (6, 4)])
+def test_a_pair_of_small_calls_has_the_bits_of_the_separate_calls(n_layers, gamma):
+    """A step's target and draft calls in one launch, any count of draft layers, 17 pairs and more (three
+    layers), both chunk sizes."""
     for lens in (SMALL, LARGE):
         B, N = len(lens), max(lens)
         qt, _, kt, _, seq, _ = _inputs(TARGET, lens, [1] * B, 1, 400)
-        nq = [6 - b % 4 for b in range(B)]
-        qd, _, kd, _, _, nqt = _inputs(DRAFT, lens, nq, 3, 401)
+        nq = [max(1, gamma - b % 4) for b in range(B)]
+        qd, _, kd, _, _, nqt = _inputs(DRAFT, lens, nq, n_layers, 401)
         st, sd = torch.full((B, 1, N), -5.0, device=DEV), torch.full((B, 1, N), -5.0, device=DEV)
         t = D.plan_score(qt[0], kt[0], seq, TARGET[3], out=st, max_len=N)
         d = D.plan_score_layers(qd, kd, seq, DRAFT[3], n_query=nqt, out=sd, max_len=N, ws_tag="score_draft")
@@ -277,3 +284,5 @@ def test_a_pair_of_small_calls_has_the_bits_of_the_separate_calls():
         D.plan_score_calls([t, d])()
         torch.cuda.synchronize()
         assert torch.equal(st, ref_t) and torch.equal(sd, ref_d)
+        for tag in ("score", "score_draft"):
+            assert int(D.score_sync_region(tag=tag).count_nonzero()) == 0
