@@ -397,12 +397,8 @@ bool score_sync_plan(const ScoreArgs& a, int32_t n_heads, int32_t nq_max, int ro
   // them.  The form keeps one workgroup on a CU for the whole call, so it is taken only
   // when every chunk the sizes allow gets a CU at once (beyond that, the two-pass form's
   // many small workgroups balance the load better).
-  int tw = (int64_t)B * max_len >= kScoreSyncPositions ? 8 : 2;
-  int64_t chunks = (max_len + 256 * tw - 1) / (256 * tw);
-  if (chunks > kScoreSyncMaxChunks && tw == 2) {  // long sequences of a small batch
-    tw = 8;
-    chunks = (max_len + 256 * tw - 1) / (256 * tw);
-  }
+  const int tw = (int64_t)B * max_len >= kScoreSyncPositions ? 8 : 2;
+  const int64_t chunks = (max_len + 256 * tw - 1) / (256 * tw);
   if (chunks > kScoreSyncMaxChunks || (int64_t)B * chunks > kScoreSyncCUs) return false;
   if ((size_t)chunks * 16 * 2 * sizeof(float) > logits_bytes) return false;
   const int64_t extent = score_extent(a, sc.kv[nu - 1], row_dim);
@@ -584,7 +580,8 @@ struct ScorePrep {
 //   single pass, 16-wave workgroups (score_sync.hip): at most 16 pairs, from 393216 positions of
 //     all sequences on while the chunks of 2048 fit the chip in one round; per-layer outputs one layer
 //     a launch (16 layers of 16 x 32768, draft: 676 us, two passes 678).  Also smaller calls of summed
-//     layers of other shapes than a draft's.
+//     layers of other shapes than a draft's.  (Long sequences of a small batch in chunks of 2048 leave
+//     CUs idle: 3 x 100000, three layers, 8 pairs 80 us, in two passes 57; 16 pairs 85 and 69.)
 //   single pass, small calls (score_once.hpp): one layer up to one 512-position chunk per CU and 65536
 //     positions of a sequence (target of 4 x 32768: 31 us, two passes 30, a launch less; draft's layer
 //     13 against 23; a sequence of 131072 in 16 per-layer outputs 250 us, two passes 178); a draft's
