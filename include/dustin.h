@@ -137,16 +137,25 @@ int32_t dustin_version(void);
  *              every call leaves them zero (the int32 at DUSTIN_SCORE_SYNC_FLAG_OFFSET
  *              aside, see below).  Calls that share a workspace must not overlap.
  * Rounding: fp32 dot products (bf16 products are exact), fp32 exp and sums.
- * Two forms compute the same sums.  When every (head, query) pair fits one 16-column
- * MFMA tile (n_heads * nq_max <= 16, scoring heads over at most 4 KV heads), groups == 1
- * and batch <= 2048, one launch does everything: each workgroup keeps the logits of a
- * chunk of positions in registers and the chunks of a sequence exchange only their
- * softmax statistics, through per-sequence counters at the start of the workspace (a
- * bounded wait; the chunks of a sequence are dispatched together and are few against the
- * GPU's compute units).  Should that wait ever time out, the kernel writes 1 to the
- * int32 at byte DUSTIN_SCORE_SYNC_FLAG_OFFSET of the workspace and its output is
+ * Several forms compute the same sums and differ by rounding.  A call's form depends on its
+ * sizes, heads and strides alone.  With groups == 1, batch <= 2048 and scoring heads over at
+ * most 4 KV heads:
+ *   - calls of at most 16 (head, query) pairs (n_heads * nq_max), and of up to 64 over two KV
+ *     heads of 64-element rows, take one launch while they are small enough (batch * max_len
+ *     of 8192 to 524288 at most, by shape), and again, at most 16 pairs, from batch * max_len
+ *     = 393216 on while every 2048 positions of a sequence get a compute unit: the workgroups
+ *     of a sequence keep their logits on chip and exchange softmax statistics;
+ *   - larger calls of 33 to 64 such pairs take one launch that reads K twice.
+ * Every other call takes two launches, the logits going through the workspace.
+ * In the one-launch forms workgroups wait for each other, for a bounded time, through the
+ * counters at the start of the workspace.  A wait can run out only beside launches on other
+ * streams that hold the compute units meanwhile.  The workgroup then does the others' part
+ * itself and the output is the same, but for two kinds of calls: those of at most 16 pairs
+ * from batch * max_len = 393216 on, and smaller ones that sum several layers of other shapes
+ * than two KV heads of 64-element rows.  Should a wait of theirs run out, the kernel writes 1
+ * to the int32 at byte DUSTIN_SCORE_SYNC_FLAG_OFFSET of the workspace and the output is
  * unspecified; zero the first DUSTIN_SCORE_SYNC_BYTES bytes again before reusing the
- * workspace.  Otherwise the logits go through the workspace in two launches.
+ * workspace.  No other call writes that flag.
  * --------------------------------------------------------------------------------- */
 #define DUSTIN_SCORE_SYNC_BYTES 16896u
 #define DUSTIN_SCORE_SYNC_FLAG_OFFSET 16384u
@@ -168,9 +177,9 @@ dustin_status dustin_score(const void* q, int64_t q_sb, int64_t q_sj, int64_t q_
  *   1 <= n_layers <= 32; n_layers * n_heads * nq_max <= 1024; batch * n_layers <= 65535
  *   workspace  dustin_score_workspace(batch, max_len, nq_max, n_heads * n_layers) bytes
  * Every other argument is as for dustin_score.  The sum over layers is accumulated in
- * fp32 together with the heads' and queries' terms and rounded once at the end.  The
- * single-pass form applies as for dustin_score (the pair limit counts one layer's pairs),
- * in one launch whatever n_layers is.
+ * fp32 together with the heads' and queries' terms and rounded once at the end.  The forms
+ * are dustin_score's (a pair limit counts one layer's pairs; K is read twice for at most
+ * three layers), the one-launch ones in one launch whatever n_layers is.
  * --------------------------------------------------------------------------------- */
 dustin_status dustin_score_layers(int32_t n_layers, const void* const* q_layers_host, int64_t q_sb,
                                   int64_t q_sj, int64_t q_sh, int32_t num_q_heads,
@@ -182,11 +191,12 @@ dustin_status dustin_score_layers(int32_t n_layers, const void* const* q_layers_
 
 /* ---------------------------------------------------------------------------------
  * dustin_score_calls -- one or two dustin_score_layers calls, such as the target's and the
- * draft's scores of one verification step (both halves of Eq. 5).  Two calls run in one
- * launch when both take the single-pass form with the pair of shapes compiled for it (the
- * first over four KV heads of 128-element rows, the second over two KV heads of 64-element
- * rows, both with the same tiles per wave): the second call's workgroups then start as the
- * first call's leave their compute units.  Otherwise the calls run one after the other.
+ * draft's scores of one verification step (both halves of Eq. 5).  Two calls of at most 16
+ * pairs run in one launch when both are small, or both large, enough for dustin_score's
+ * one-launch forms, the first is one layer over one, two or four KV heads (large: any number
+ * of layers over four) of 128-element rows, and the second is any number of layers over two KV
+ * heads of 64-element rows (small: also three layers of 17 to 32 pairs).  Otherwise the calls
+ * run one after the other.
  * Either way each output has the same bits as the corresponding dustin_score_layers call.
  *   calls    host array of n_calls (1 or 2) descriptors; each holds the arguments of one
  *            dustin_score_layers call (n_layers = 1 is a dustin_score call), with a
@@ -224,7 +234,7 @@ typedef struct {
 dustin_status dustin_score_calls(int32_t n_calls, const dustin_score_call* calls, void* stream);
 
 /* ---------------------------------------------------------------------------------
- * dustin_score_per_layer -- Eq. 5 for n_layers layers in two launches, each layer into
+ * dustin_score_per_layer -- Eq. 5 for n_layers layers in few launches, each layer into
  * its own output: the per-layer, per-head relevance of the SpecAttn-style selection the
  * paper compares with (appendix on SpecAttn: every draft layer and head scores tokens for
  * its own target layers, with no aggregation across layers).
@@ -233,7 +243,9 @@ dustin_status dustin_score_calls(int32_t n_calls, const dustin_score_call* calls
  * There is no init.  1 <= n_layers <= 32; n_heads * nq_max <= 1024; batch * n_layers <=
  * 65535; groups * n_layers <= 65535; workspace as for dustin_score_layers.  Every other
  * argument is as for dustin_score_layers.  Each layer's output has the same bits as a
- * dustin_score call on that layer alone.
+ * dustin_score call on that layer alone.  Launches: two where that call takes two; where it
+ * takes one, one for every 2048 (layer, sequence) pairs, but one a layer for at most 16 pairs
+ * from batch * max_len = 393216 on.
  * --------------------------------------------------------------------------------- */
 dustin_status dustin_score_per_layer(int32_t n_layers, const void* const* q_layers_host, int64_t q_sb,
                                      int64_t q_sj, int64_t q_sh, int32_t num_q_heads,

@@ -206,8 +206,8 @@ def workspace(nbytes: int, device, tag: str, stream=None) -> Optional[torch.Tens
     return buf[off:off + nbytes]
 
 
-# Layout of a score workspace's first bytes (include/dustin.h): per-sequence counters of
-# the single-pass form, zero between calls, and its timeout flag.
+# Layout of a score workspace's first bytes (include/dustin.h): counters of the one-launch
+# forms, zero between calls, and a timeout flag.
 SCORE_SYNC_BYTES = 16896
 SCORE_SYNC_FLAG_OFFSET = 16384
 
@@ -437,7 +437,7 @@ def plan_score_per_layer(qs: Sequence[torch.Tensor], ks: Sequence[torch.Tensor],
                          max_len: Optional[int] = None, page_table: Optional[torch.Tensor] = None,
                          stream=None) -> Call:
     """Prepared dustin_score_per_layer: Eq. 5 of each layer (qs[l], ks[l]) into out[l]
-    (fp32 [L, B, groups, max_len]), in two launches."""
+    (fp32 [L, B, groups, max_len]), in few launches."""
     if len(qs) != len(ks) or not qs:
         raise ValueError("one query tensor per cache, at least one layer")
     _on_gpu(*qs, *ks, out, page_table)

@@ -1,6 +1,6 @@
 // score_sync.hip -- Eq. 5 in one pass, for calls whose (head, query) pairs fit one MFMA
-// column tile and whose chunks fill the chip in one round (score_once.hpp takes the smaller ones
-// of the common shapes).
+// column tile and whose chunks fill the chip in one round (score_once.hpp takes the smaller ones,
+// but for several summed layers of other shapes than a draft's).
 //
 // The two-pass form (score.hip) writes every pair's logits to the workspace and reads them
 // back, because the softmax of Eq. 5 needs each pair's max and sum over all N_b positions
@@ -21,8 +21,10 @@
 //   * The chunks of a sequence have consecutive block ids, so each XCD dispatches them after
 //     every chunk of the earlier sequences: a waiting chunk only waits for chunks that hold a
 //     CU or get one as earlier sequences finish (the host keeps G_b far below the CUs of the
-//     chip).  The wait is bounded anyway: on a timeout the workgroup sets a flag in the
-//     workspace and goes on.
+//     chip).  That holds for a launch by itself; beside launches on other streams whose
+//     workgroups wait too, each may hold CUs of some XCD that the other needs.  The wait is
+//     bounded: on a timeout the workgroup sets a flag in the workspace and goes on, and the
+//     output is unspecified.
 //   * The next layer's first K rows and its queries are in flight across the wait.
 //   * The last chunk of a sequence to leave returns the sequence's counters to zero.
 #include <type_traits>

@@ -120,7 +120,7 @@ class PerLayerSelectionStep:
     """The SpecAttn-style step the paper compares with (appendix on SpecAttn): token relevance
     from every head of every draft layer, one index set per draft layer (no aggregation
     across layers), each target layer attending with the set of its depth-matched draft
-    layer.  Launches: the per-layer draft scores (two), one top-k over (draft layer, sequence)
+    layer.  Launches: the per-layer draft scores (one or two, as a rule), one top-k over (draft layer, sequence)
     rows, then per target layer the sparse attention.  est holds the draft model's layers
     (draft_q, draft_k); n_target is the target model's depth for the layer matching."""
 

@@ -1,4 +1,5 @@
-"""The single-pass form of Eq. 5 (score_sync.hip) against the oracle: every number of
+"""The single-pass forms of Eq. 5 (score_sync.hip at full size and for several layers of other shapes
+than a draft's, score_once.hpp for the other small calls) against the oracle: every number of
 used KV heads, both row lengths, ragged batches with empty and one-position sequences,
 sequences of one chunk and of several, per-sequence query counts, paged caches with pages
 smaller and larger than a 16-position tile, several layers in one call, and the counter
@@ -171,7 +172,8 @@ def _step_scores(B, N, lens, gamma, page_size=0, seed=70):
 def test_two_calls_in_one_launch_equal_the_separate_calls(B, N, page_size):
     """dustin_score_calls with the target's and the draft's calls of a step: the outputs have
     the bits of the two calls made one after the other (one launch at the full shape, where
-    both take the single-pass form with eight tiles per wave; two tiles per wave below)."""
+    both take the single-pass form with eight tiles per wave, and below, where both are small
+    calls of score_once.hpp)."""
     lens = [N - 37 * b for b in range(B)]
     pt_, pd_, st, sd = _step_scores(B, N, lens, 4, page_size)
     pt_()
