@@ -359,6 +359,29 @@ int64_t score_extent(const ScoreArgs& a, int last_kv, int row_dim) {
   return rows_bytes < 0 || extent > INT32_MAX ? -1 : extent;
 }
 
+// The KV heads that a call's heads use in ascending order, and the (head, query) pairs of each;
+// returns their number, 0 when there are more than four.
+int score_used_kv(const ScoreArgs& a, int32_t n_heads, int32_t nq_max, int32_t (&kv)[4], int (&pairs)[4]) {
+  int nu = 0;
+  for (int i = 0; i < n_heads; ++i) {
+    const int g = a.heads[i] / a.group_size;
+    int at = 0;
+    while (at < nu && kv[at] < g) ++at;
+    if (at == nu || kv[at] != g) {
+      if (nu == 4) return 0;
+      for (int v = nu; v > at; --v) {
+        kv[v] = kv[v - 1];
+        pairs[v] = pairs[v - 1];
+      }
+      kv[at] = g;
+      pairs[at] = 0;
+      ++nu;
+    }
+    pairs[at] += nq_max;
+  }
+  return nu;
+}
+
 // The single-pass form (score_sync.hip) for a call with at most 16 (head, query) pairs over
 // at most 4 KV heads and one output group (a's heads, layers, cache view, dims, output and
 // workspace fields set): fills sc and returns true, or false when it does not take the call.
@@ -369,18 +392,9 @@ bool score_sync_plan(const ScoreArgs& a, int32_t n_heads, int32_t nq_max, int ro
   if (row_dim != 64 && row_dim != 128) return false;
   if ((int64_t)n_heads * nq_max > 16) return false;
   memset(&sc, 0, sizeof sc);
-  // used KV heads in ascending order; columns KV head by KV head, then head slot, then query
-  int nu = 0;
-  for (int i = 0; i < n_heads; ++i) {
-    const int g = a.heads[i] / a.group_size;
-    int at = 0;
-    while (at < nu && sc.kv[at] < g) ++at;
-    if (at < nu && sc.kv[at] == g) continue;
-    if (nu == 4) return false;
-    for (int v = nu; v > at; --v) sc.kv[v] = sc.kv[v - 1];
-    sc.kv[at] = g;
-    ++nu;
-  }
+  // columns KV head by KV head, then head slot, then query
+  int pairs[4];
+  const int nu = score_used_kv(a, n_heads, nq_max, sc.kv, pairs);
   if (nu == 0) return false;
   int np = 0;
   for (int u = 0; u < nu; ++u)
@@ -440,24 +454,9 @@ bool score_chunk_call(const ScoreArgs& a, int32_t n_heads, int32_t nq_max, int r
                       ChunkCall& cc) {
   if (a.page_mode || groups != 1 || (row_dim != 64 && row_dim != 128)) return false;
   memset(&cc, 0, sizeof cc);
-  // used KV heads in ascending order, and the pairs of each
-  int nu = 0, pairs[4] = {0, 0, 0, 0};
-  for (int i = 0; i < n_heads; ++i) {
-    const int g = a.heads[i] / a.group_size;
-    int at = 0;
-    while (at < nu && cc.kv[at] < g) ++at;
-    if (at == nu || cc.kv[at] != g) {
-      if (nu == 4) return false;
-      for (int v = nu; v > at; --v) {
-        cc.kv[v] = cc.kv[v - 1];
-        pairs[v] = pairs[v - 1];
-      }
-      cc.kv[at] = g;
-      pairs[at] = 0;
-      ++nu;
-    }
-    pairs[at] += nq_max;
-  }
+  int pairs[4];
+  const int nu = score_used_kv(a, n_heads, nq_max, cc.kv, pairs);
+  if (nu == 0) return false;
   // one column tile for all KV heads where every pair fits it, else nt for each KV head
   int nt = 0;
   if (n_heads * nq_max > 16)

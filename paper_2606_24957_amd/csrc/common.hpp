@@ -82,6 +82,17 @@ __device__ __forceinline__ float sum_over_lane_groups(float x) { return sum_xor3
 // 2^x on the hardware exp unit (results below 2^-126 flush to zero).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// A pair of floats past the caches (agent scope), as one 64-bit access.
+__device__ __forceinline__ float2 load_pair_sc1(const float2* p) {
+  const uint64_t u = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+  return make_float2(__uint_as_float((uint32_t)u), __uint_as_float((uint32_t)(u >> 32)));
+}
+__device__ __forceinline__ void store_pair_sc1(float2* p, float m, float s) {
+  const uint64_t u = (uint64_t)__float_as_uint(m) | ((uint64_t)__float_as_uint(s) << 32);
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
 // Per-sequence sizes read from the device arrays and clamped to the host-checked bounds.

@@ -25,22 +25,13 @@ constexpr int kChunkThreads = kChunkWaves * kWave;
 constexpr int kChunkMaxCols = 96;     // columns of one publish: layers held at once times column tiles times 16
 constexpr int kChunkMergeLoads = 8;   // summaries a thread loads at once when it merges
 
-// (m, s) <- the union of two (max, sum of exp2(x - max)) summaries
+// (m, s) <- the union of two (max, sum of exp2(x - max)) summaries (score_sync.hip has its own, with
+// the fusing left to the compiler)
 __device__ __forceinline__ void merge_ms(float& m, float& s, float mo, float so) {
   const float mn = fmaxf(m, mo);
   const float mu = mn == -INFINITY ? 0.f : mn;
   s = fmaf(so, fast_exp2(mo - mu), s * fast_exp2(m - mu));
   m = mn;
-}
-
-__device__ __forceinline__ float2 load_pair_sc1(const float2* p) {
-  const uint64_t u = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-  return make_float2(__uint_as_float((uint32_t)u), __uint_as_float((uint32_t)(u >> 32)));
-}
-__device__ __forceinline__ void store_pair_sc1(float2* p, float m, float s) {
-  const uint64_t u = (uint64_t)__float_as_uint(m) | ((uint64_t)__float_as_uint(s) << 32);
-  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Sum over the 16 lanes of a row (rotations by 8, 4, 2, 1), the same in every lane.

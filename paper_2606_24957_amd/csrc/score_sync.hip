@@ -46,16 +46,6 @@ __device__ __forceinline__ void merge_ms(float& m, float& s, float mo, float so)
   m = mn;
 }
 
-__device__ __forceinline__ float2 load_pair_sc1(const float2* p) {
-  const uint64_t u = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-  return make_float2(__uint_as_float((uint32_t)u), __uint_as_float((uint32_t)(u >> 32)));
-}
-__device__ __forceinline__ void store_pair_sc1(float2* p, float m, float s) {
-  const uint64_t u = (uint64_t)__float_as_uint(m) | ((uint64_t)__float_as_uint(s) << 32);
-  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 }  // namespace
 
 // LDS of a single-pass workgroup: the chunk's logits column by column, a pitch of C + 4
