@@ -587,10 +587,11 @@ struct ScorePrep {
 //     summed layers up to two chunks per CU (8 x 32768, two layers 33 us against 43, three 43 against 60,
 //     four 53 against 89, five 94 against 108; with at most four pairs, whose logits are few, up to one:
 //     5 x 32768 39 us against 34), and three layers of 17 to 32 pairs, whose logits
-//     make two passes longer, up to four (8 x 65536, 24
-//     pairs: 116 us against 155; past them a ragged batch has several rounds of workgroups
-//     of sequences that end apart, 177 us against 164 at 16 x up to 62922).  Chunks of 256 positions fill
-//     the chip better up to 32768 positions (target and draft 21 us against 24), those of 512 beyond.
+//     make two passes longer, up to four (8 x 65536, 24 pairs: 115 us against 153; the line is where it
+//     was drawn while the units' counters lay together, which made several rounds of workgroups
+//     slower than two passes, 177 us against 164 at 16 x up to 62922: 159 and 211 with the counters apart).
+//     Chunks of 256 positions fill the chip better up to 32768 positions (target and draft, 4 x 8192: 17
+//     us against 23), those of 512 beyond (2 x 32768: 30 against 34).
 //     Single layers of more than 16 pairs: up to 8192 positions.
 //   K read twice (score_reread.hip): 33 to 64 pairs from 131072 positions on, below 48 pairs from
 //     262144 (16 layers of 4 x 32768, 56 pairs: 210 us, two passes 366; 4 layers of 16 x up to 8192, 36
@@ -655,8 +656,9 @@ ChunkArgs score_chunk_args(const ChunkCall* c0, const ChunkCall* c1, bool reread
     ca.call[n++].sync_stride = stride < kChunkSyncStride ? stride : kChunkSyncStride;
   }
   // the second kind's blocks come `lag` units behind the first's: about as many blocks as the
-  // chip holds, so that they find their columns merged (16 x 32768 positions, 4 layers: 252 us;
-  // a quarter of that lag 344)
+  // chip holds, so that they find their columns merged (56 pairs, 4 layers of 4 x 32768 positions: 56
+  // us; half the lag 61, a quarter 64; of 16 x 16384, 104, 108, 113; 24 layers of 16 x 32768, where K is
+  // more than the memory-side cache holds, 1124, 1050, 1045)
   const int64_t blocks = (int64_t)(c0->per_layer ? 1 : c0->n_layers) * c0->chunks;
   int64_t lag = (4 * kScoreSyncCUs + blocks - 1) / blocks;
   if (lag > ca.units) lag = ca.units;

@@ -170,7 +170,7 @@ constexpr int kChunkMaxOnce = 256;         // most chunks of a sequence in score
 // Most int32 between the counters of two units: as far apart as the region allows, so that the
 // polls and counts of one unit's workgroups do not queue behind another's in a cache line and memory
 // channel (per-layer calls of 16 units of 8192 positions, 28 pairs: adjacent 26.3 us, apart 14.7;
-// score_reread.hip, 24 layers of 16 x 16384, 56 pairs: 866 us, 624).
+// score_reread.hip, 24 layers of 16 x 16384, 56 pairs: 866 us, 640).
 constexpr int kChunkSyncStride = 64;
 // Looks at a counter (each a memory round trip) before a wait ends: some milliseconds, where calls that
 // share the chip with nobody need up to 512 (24 pairs, three layers of 16 x up to 32768, several rounds

@@ -10,10 +10,10 @@
 //   * it merges the G summaries in a fixed order, and every position gets
 //     sum_columns exp2(x - M) / Z, one multiply-add per logit.
 // Bound by its chain of memory round trips (rows, publish, count, summaries), which is why the
-// chunks are small (the rows stream over all CUs), the three draft layers share one publish and
+// chunks are small (the rows stream over all CUs), up to four draft layers share one publish and
 // wait, and a step's two calls one launch.  16-wave workgroups of 512 positions that waited
-// once per layer, in two launches, took 22 + 36 us for a step of 4 x 8192 positions over two
-// target and three draft KV heads' layers, now 19 in one; one sequence of 32768 took 49, now 21.
+// once per layer, in two launches, took 55 us for a step's scores of 4 x 8192 positions, over two
+// KV heads of the target and three draft layers, now 15 in one; one sequence of 32768 took 73, now 19.
 //
 // A wait ends without a cooperative launch: workgroups are dispatched in id order on each XCD, and a
 // unit's chunks have consecutive ids, so that they hold slots or are next in line.  But workgroups of
@@ -33,9 +33,9 @@ namespace {
 
 // Chunks times columns up to which every workgroup merges all summaries itself: four rounds of
 // loads, beyond which they cost more than another hand-off while no workgroup waits for a slot (one
-// sequence of 131072 positions, three layers, 24 pairs: 44.9 us, shared 37.7).  With several rounds
+// sequence of 131072 positions, three layers, 24 pairs: 41.7 us, shared 38.3).  With several rounds
 // of workgroups the hand-off's round trips under load cost more than the loads do (8 x 65536:
-// 127 us, shared 153), and the host leaves share_merge unset.
+// 116 us, shared 123), and the host leaves share_merge unset.
 constexpr int kMergeAll = 4 * kChunkThreads * kChunkMergeLoads;
 
 // Column col's (M, 1 / Z) over the unit's G chunks, by one wave (lane 0 holds it).
