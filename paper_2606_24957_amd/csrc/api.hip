@@ -111,8 +111,9 @@ struct AttnSplits {
 // that share the merge wait for each other.  Each split at least eight steps (two per wave) for
 // the longest pair, or four (one per wave) where eight splits or more leave that little: one
 // sequence, 8 KV heads of 40 rows, 2048 tokens in 16 splits of four steps 14.7 us, 8 of eight 15.2,
-// 1 of 64 29.8; 1024 in 8 of four 13.5, 4 of eight 15.8.  From sixteen steps on, eight splits of
-// two: 512 tokens 13.2 us, 4 of four 14.2, one 14.2.  Below, one: 256 tokens, one KV head, 10.9, 4 of
+// 1 of 64 29.8; 1024 in 8 of four 13.5, 4 of eight 15.8.  From seventeen steps on, eight splits of
+// two: 512 tokens 13.2 us, 4 of four 14.2, one 14.2; sixteen steps in two of eight, 13.4 (8 of two 13.8;
+// two sequences of 480 and 266 tokens 15.0 and 16.1).  Below, one: 256 tokens, one KV head, 10.9, 4 of
 // two 13.9.
 // The slots that the pairs leave over go to the longer pairs of a ragged batch; where pairs of equal
 // length have one split, from 64 steps on (20 sequences of 8 KV heads: one of 2048 tokens and 19 of 256
@@ -133,7 +134,7 @@ AttnSplits attn_splits(int batch, int num_kv_heads, int64_t tokens_per_pair, boo
     min_steps = 1;
   } else {
     s = kAttnBalancePairs / pairs;
-    if (fine && s >= 8 && steps >= 16) min_steps = steps >= 32 ? 4 : 2;
+    if (fine && s >= 8 && steps > 16) min_steps = steps >= 32 ? 4 : 2;
     int64_t most = steps / min_steps;
     if (min_steps == 2) most = 8;
     if (s > most) s = most;
