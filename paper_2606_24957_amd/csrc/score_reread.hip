@@ -9,8 +9,8 @@
 //     the columns' (M, 1 / Z).
 //   * second: per (sequence, chunk), waits until the sequence's layers are merged, forms the
 //     logits again from K and adds up sum_columns exp2(x - M) / Z over the layers.
-// Bound by the reads of K: 24 layers of 16 x 32768 positions and 56 pairs (3.2 GB of K) take 1124 us,
-// 5.7 TB/s over both reads, against 1446 + 571 with the logits written and read.
+// Bound by the reads of K: 24 layers of 16 x 32768 positions and 56 pairs (3.2 GB of K, 6.5 read from
+// HBM) take 1.12 to 1.23 ms, 5.3 to 5.7 TB/s, against 1446 + 571 us with the logits written and read.
 //
 // The second kind's blocks of a unit (a sequence, or a (layer, sequence)) follow the first kind's of
 // the unit `lag` later, so that they rarely wait.  The first kind waits for nothing, and on each XCD
